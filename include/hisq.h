@@ -37,7 +37,11 @@
  * Memory and streams: every data pointer is a DEVICE pointer on the current
  * HIP device unless stated otherwise.  The caller owns its buffers; the library
  * never frees them and keeps no reference after a call returns.  A gauge handle
- * owns the library's own packed link copies and solver workspaces.  `stream`
+ * owns the library's own packed link copies and solver workspaces.  Memory of
+ * destroyed handles and finished calls is kept for the library's next
+ * allocations: at most 16 GiB, freed when an allocation of the library fails
+ * and, if nobody wanted it for five seconds, by the next call that allocates.
+ * `stream`
  * is a hipStream_t (NULL = the default stream).  Dslash calls are asynchronous
  * on that stream; solvers order themselves after prior work on it and return
  * when x is written (synchronous).

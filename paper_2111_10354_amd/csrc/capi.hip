@@ -82,6 +82,14 @@ hisq_gauge_s::~hisq_gauge_s() {
     if (diag_event) (void)hipEventDestroy(diag_event);
 }
 
+void hisq_gauge_s::recycle() {
+    for (auto &f : links)
+        for (auto &b : f) b.recycle();
+    recycle_all(diag_buf, thin);
+    for (auto &w : cg_ws) w.second->recycle();
+    if (fcg_ws) fcg_ws->recycle();
+}
+
 extern "C" {
 
 int hisq_version(void) { return HISQ_VERSION; }
@@ -196,6 +204,7 @@ int hisq_gauge_create(hisq_gauge_t *out, const int dims[4], const double *fat, c
         delete g;
         return fail(HISQ_ERR_HIP, std::string("create: ") + hipGetErrorString(e));
     }
+    maxabs.recycle();  // the stream has ended
     *out = g;
     return HISQ_OK;
 }
@@ -217,7 +226,7 @@ int hisq_smear_links(const int dims[4], const double *thin, double *fat, double 
 
 int hisq_gauge_destroy(hisq_gauge_t g) {
     if (!g) return HISQ_OK;
-    (void)hipDeviceSynchronize();
+    if (hipDeviceSynchronize() == hipSuccess) g->recycle();
     delete g;
     return HISQ_OK;
 }

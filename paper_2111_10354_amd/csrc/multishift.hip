@@ -382,6 +382,7 @@ static int multishift_solve_lockstep(hisq_gauge_s *g, double mass, int m, int ns
             HISQ_HIP_CHECK(hipMemcpyAsync((char *)x + s64 * ((size_t)j * ns + order[k]),
                                           (char *)x64.p + s64 * ((size_t)k * m + j), s64, hipMemcpyDeviceToDevice, s));
     HISQ_HIP_CHECK(hipStreamSynchronize(s));
+    recycle_all(rk, tk, qk, pk, xk, x64, t64, ax64, r64, part, state, msb, glb, diag, scal, bstack);
     const double total_ms = std::chrono::duration<double, std::milli>(clk::now() - t0).count();
     if (trace) {
         int most = 0;
@@ -554,6 +555,7 @@ int multishift_solve(hisq_gauge_s *g, double mass, int ns, const double *shifts,
         HISQ_HIP_CHECK(hipMemcpyAsync((char *)x + s64 * order[k], (char *)xs.p + s64 * k, s64,
                                       hipMemcpyDeviceToDevice, s));
     HISQ_HIP_CHECK(hipStreamSynchronize(s));
+    recycle_all(w.t, w.q, w.r, w.pk, w.part, w.state, w.ms, w.gl, w.diag, w.bstack, xs, scal);
     const double total_ms = std::chrono::duration<double, std::milli>(clk::now() - t0).count();
     if (stats) {
         for (int k = 0; k < ns; ++k) {

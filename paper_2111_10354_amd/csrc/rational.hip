@@ -557,6 +557,7 @@ int rational_apply(hisq_gauge_s *g, double mass, int nsrc, double alpha0, int n,
                            (const d2v *)((const char *)xs.p + s64 * (size_t)n * j), (d2v *)((char *)out + s64 * j));
     HISQ_HIP_CHECK(hipGetLastError());
     HISQ_HIP_CHECK(hipStreamSynchronize(s));
+    recycle_all(xs, al);
     return worst;
 }
 
@@ -597,6 +598,7 @@ int spectral_bounds(hisq_gauge_s *g, double mass, int iters, double *lmin, doubl
     }
     HISQ_HIP_CHECK(hipMemcpyAsync(&rq, (double *)scal.p + 1, sizeof(double), hipMemcpyDeviceToHost, s));
     HISQ_HIP_CHECK(hipStreamSynchronize(s));
+    recycle_all(v, t, av, part, scal, diag);
     *lmin = d;
     *lmax = rq;
     return HISQ_OK;

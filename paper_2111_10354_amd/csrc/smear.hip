@@ -321,6 +321,7 @@ int smear_links(const int dims[4], const double *thin, double *fat, double *lng,
     HISQ_HIP_CHECK(hipGetLastError());
     // the temporaries are freed on return: wait for the kernels that use them
     HISQ_HIP_CHECK(hipStreamSynchronize(s));
+    recycle_all(w, t1, t2);
     return HISQ_OK;
 }
 

@@ -27,24 +27,6 @@
 
 namespace hisq {
 
-int DevBuf::alloc(size_t n) {
-    if (p && bytes >= n) return HISQ_OK;
-    if (p) {
-        (void)hipFree(p);
-        p = nullptr;
-        bytes = 0;
-    }
-    if (n == 0) return HISQ_OK;
-    hipError_t e = hipMalloc(&p, n);
-    if (e != hipSuccess) {
-        p = nullptr;
-        set_error(std::string("hipMalloc(") + std::to_string(n) + "): " + hipGetErrorString(e));
-        return e == hipErrorOutOfMemory ? HISQ_ERR_OOM : HISQ_ERR_HIP;
-    }
-    bytes = n;
-    return HISQ_OK;
-}
-
 static size_t real_bytes(int f) { return f == F64 ? 8 : f == F32 ? 4 : 2; }
 
 size_t dslash_algorithmic_bytes(int fl, int fi, int fo, int64_t vh, int nrhs, bool epi, int comp) {

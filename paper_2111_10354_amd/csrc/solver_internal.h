@@ -75,18 +75,28 @@ void launch_zero(int fmt, int vh, int n, void *v, hipStream_t s);
 void launch_reduce(int which, int n, const double *part, int nb, CgState *st, double *out, hipStream_t s);
 void launch_resume_flags(int n, CgState *st, hipStream_t s);
 
-// Device allocation owned by the handle.
+// Device allocation owned by a handle, a workspace or a call (devmem.hip).  The
+// contents of a new one are undefined.  recycle() keeps the block for a later
+// allocation: only when no work on it is pending on any stream.
 struct DevBuf {
     void *p = nullptr;
-    size_t bytes = 0;
+    size_t bytes = 0;  // as asked for
+    size_t held = 0;   // of the block
+    int device = -1;
     DevBuf() = default;
     DevBuf(const DevBuf &) = delete;
     DevBuf &operator=(const DevBuf &) = delete;
-    ~DevBuf() {
-        if (p) (void)hipFree(p);
-    }
+    ~DevBuf() { release(); }
     int alloc(size_t n);
+    void release();
+    void recycle();
 };
+
+// Recycles buffers of a call that has waited for its stream.
+template <class... B>
+inline void recycle_all(B &...b) {
+    (b.recycle(), ...);
+}
 
 // Tuned launch shape of the Dslash for one (precision pair, nrhs).
 struct DslashShape {
@@ -118,6 +128,9 @@ struct CgWorkspace {
     void *T() { return fmt == F64 ? t64.p : ts.p; }
     void *Q() { return fmt == F64 ? q64.p : qs.p; }
     CgState *st() { return (CgState *)state.p; }
+    void recycle() {
+        recycle_all(b64, x64, r64, t64, ax64, p64, q64, xs, rs, ps, ts, qs, part, state, diag, scal);
+    }
 };
 
 // Buffers, device state and the captured iteration graph of flexible CG.
@@ -133,6 +146,9 @@ struct FcgWorkspace {
     FcgWorkspace(const FcgWorkspace &) = delete;
     FcgWorkspace &operator=(const FcgWorkspace &) = delete;
     ~FcgWorkspace();
+    void recycle() {
+        recycle_all(b64, x64, r64, t64, ax64, xs, rs, ps, qs, zs, ts, part, part2, state, diag, scal);
+    }
 };
 
 }  // namespace hisq
@@ -152,6 +168,7 @@ struct hisq_gauge_s {
     std::map<std::tuple<int, int, int, int, int>, hisq::DslashShape> shapes;
     std::map<std::tuple<int, int, int>, std::unique_ptr<hisq::CgWorkspace>> cg_ws;  // (n, fmt | links << 4, chunk)
     std::unique_ptr<hisq::FcgWorkspace> fcg_ws;
+    void recycle();  // the device is idle
     ~hisq_gauge_s();
 };
 
