@@ -151,7 +151,8 @@ int hisq_gauge_create(hisq_gauge_t *out, const int dims[4], const double *fat, c
  *   fat, lng  device outputs in the same layout; none of the three may overlap
  *   flags     HISQ_SMEAR_ANTIPERIODIC_T: fold the antiperiodic time boundary
  *             sign (-1 on t links with t + 1 >= Lt, Naik links t + 3 >= Lt)
- * Allocates a workspace of 6 link fields of one direction (864 V bytes) for
+ * fat and lng hold intermediate fields until the call returns.  Allocates a
+ * workspace of 6 link fields of one direction (864 V bytes) for
  * the call.  Synchronous.  Errors: -1 bad dims, pointers, flags or overlap,
  * -3 out of memory, -2 HIP failure.
  */
