@@ -159,6 +159,7 @@ int hisq_gauge_create(hisq_gauge_t *out, const int dims[4], const double *fat, c
         }
         g->comp_mode = defect[0] <= 1e-12f ? COMP_SIGN : defect[1] <= 1e-12f ? COMP_KAPPA : COMP_NONE;
     }
+    void *dst[3][2] = {};
     for (int f = 0; f < 3; ++f) {
         if (!(prec_mask & HISQ_PREC_MASK(f))) continue;
         const size_t bytes = link_parity_bytes(f, g->geom.vh, links_compressed(g, f));
@@ -166,30 +167,27 @@ int hisq_gauge_create(hisq_gauge_t *out, const int dims[4], const double *fat, c
             delete g;
             return rc;
         }
-        float *mb = nullptr;
-        if (f == H16) {
-            e = hipMemsetAsync(maxabs.p, 0, sizeof(float), s);
-            mb = (float *)maxabs.p;
-        }
-        if (e == hipSuccess)
-            rc = launch_pack_links(g->geom, f, fat, lng, g->links[f][0].p, g->links[f][1].p, mb,
-                                   links_compressed(g, f), s);
-        if (e != hipSuccess || rc) {
+        for (int par = 0; par < 2; ++par) dst[f][par] = g->links[f][par].p;
+    }
+    const bool check16 = (prec_mask & HISQ_PREC_MASK(H16)) != 0;
+    e = check16 ? hipMemsetAsync(maxabs.p, 0, sizeof(float), s) : hipSuccess;
+    if (e == hipSuccess)
+        rc = launch_pack_links(g->geom, fat, lng, dst, check16 ? (float *)maxabs.p : nullptr, g->comp_mode, s);
+    if (e != hipSuccess || rc) {
+        delete g;
+        return rc ? rc : fail(HISQ_ERR_HIP, hipGetErrorString(e));
+    }
+    if (check16) {
+        float m = 0.f;
+        e = hipMemcpyAsync(&m, maxabs.p, sizeof(float), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e != hipSuccess) {
             delete g;
-            return rc ? rc : fail(HISQ_ERR_HIP, hipGetErrorString(e));
+            return fail(HISQ_ERR_HIP, hipGetErrorString(e));
         }
-        if (f == H16) {
-            float m = 0.f;
-            e = hipMemcpyAsync(&m, maxabs.p, sizeof(float), hipMemcpyDeviceToHost, s);
-            if (e == hipSuccess) e = hipStreamSynchronize(s);
-            if (e != hipSuccess) {
-                delete g;
-                return fail(HISQ_ERR_HIP, hipGetErrorString(e));
-            }
-            if (!(m < 16384.f)) {
-                delete g;
-                return fail(HISQ_ERR_INVALID, "link entries too large (or non-finite) for FP16 storage");
-            }
+        if (!(m < 16384.f)) {
+            delete g;
+            return fail(HISQ_ERR_INVALID, "link entries too large (or non-finite) for FP16 storage");
         }
     }
     e = hipStreamCreateWithFlags(&g->capture_stream, hipStreamNonBlocking);

@@ -526,9 +526,11 @@ const char *get_error();
     } while (0)
 
 // ------------------------------------------------------------------ launch wrappers
-// Link packing: canonical [V][4][3][3] complex double -> packed per parity.
-int launch_pack_links(const Geom &g, int fmt, const double *fat, const double *lng, void *dst_even,
-                      void *dst_odd, float *maxabs_dev, int comp_mode, hipStream_t s);
+// Link packing: canonical [V][4][3][3] complex double -> packed, one launch for
+// every [format][output parity] with memory; comp_mode: layout of the FP32 and
+// FP16 copies; maxabs_dev (may be null): atomic max of the entries' magnitudes.
+int launch_pack_links(const Geom &g, const double *fat, const double *lng, void *const dst[3][2], float *maxabs_dev,
+                      int comp_mode, hipStream_t s);
 // Largest deviation of any long link from a unitary matrix with determinant
 // +-1 (max |L L^+ - 1| entry or | det - round(det) |) into defect_bits[0], and
 // from a positive multiple s U of a unitary U (max |L L^+ - s^2| entry / s^2,
