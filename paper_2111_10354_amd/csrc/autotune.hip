@@ -135,6 +135,8 @@ static std::vector<int> brick_orders(const Geom &G, int fi, int tile) {
 static int shape_rsplit(const DslashShape &s) { return 1 << ((s.order >> 24) & 3); }
 
 static bool valid_shape(const Geom &geom, int fl, int nrhs, const DslashShape &s) {
+    if (const int w = shared_waves(s.order))  // a wave without a right-hand side only repeats another's work
+        return shared_built(s.tile, w) && s.tile * (w - 1) < nrhs && order_supported(geom, s.order, s.block);
     if (s.tile < 1 || s.tile > 16 || (s.tile & (s.tile - 1)) || s.tile > std::max(1, nrhs)) return false;
     if (fl == F64 && s.tile > 4) return false;
     if ((s.order & 0xff) == 4 && s.tile > 4) return false;  // t-march: RHS tiles of up to 4
@@ -199,6 +201,8 @@ int tune_dslash(hisq_gauge_s *g, int fl, int fi, int fo, int nrhs, bool epi, con
         a.block = sh.block;
         a.order = sh.order;
         a.compressed = links_compressed(g, fl);
+        a.cached = links_cached(g, fl);
+        a.tiles = (const int *)g->tile_order.p;
         return launch_dslash(G, a, s);
     };
 
@@ -235,6 +239,16 @@ int tune_dslash(hisq_gauge_s *g, int fl, int fi, int fo, int nrhs, bool epi, con
             c.tile = tile;
             c.block = block;
             c.order = 3;
+            if (valid_shape(G, fl, nrhs, c)) cands.push_back(c);
+        }
+
+    for (int tile : {1, 2, 3, 4})  // links shared through LDS by the waves of a site tile
+        for (int waves : {2, 3, 4}) {
+            if (waves == 3 && nrhs <= 4) continue;
+            DslashShape c;
+            c.tile = tile;
+            c.block = 64 * waves;
+            c.order = shared_order(waves);
             if (valid_shape(G, fl, nrhs, c)) cands.push_back(c);
         }
 

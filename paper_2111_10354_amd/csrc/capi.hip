@@ -85,7 +85,7 @@ hisq_gauge_s::~hisq_gauge_s() {
 void hisq_gauge_s::recycle() {
     for (auto &f : links)
         for (auto &b : f) b.recycle();
-    recycle_all(diag_buf, thin);
+    recycle_all(tile_order, diag_buf, thin);
     for (auto &w : cg_ws) w.second->recycle();
     if (fcg_ws) fcg_ws->recycle();
 }
@@ -192,6 +192,15 @@ int hisq_gauge_create(hisq_gauge_t *out, const int dims[4], const double *fat, c
     }
     e = hipStreamCreateWithFlags(&g->capture_stream, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&g->diag_event, hipEventDisableTiming);
+    std::vector<int> order((g->geom.vh + 63) / 64);  // lives until the stream is waited for below
+    if (e == hipSuccess) {
+        link_tile_order(g->geom, order.data());
+        if ((rc = g->tile_order.alloc(sizeof(int) * order.size()))) {
+            delete g;
+            return rc;
+        }
+        e = hipMemcpyAsync(g->tile_order.p, order.data(), sizeof(int) * order.size(), hipMemcpyHostToDevice, s);
+    }
     // epilogue coefficients of up to 64 right-hand sides without a later allocation
     if (e == hipSuccess && (rc = g->diag_buf.alloc(sizeof(double) * 64))) {
         delete g;
@@ -239,7 +248,7 @@ int hisq_gauge_device_bytes(hisq_gauge_t g, size_t *bytes) {
     int rc = check_handle(g);
     if (rc) return rc;
     if (!bytes) return fail(HISQ_ERR_INVALID, "bytes is NULL");
-    size_t n = g->diag_buf.bytes;
+    size_t n = g->diag_buf.bytes + g->tile_order.bytes;
     for (auto &f : g->links)
         for (auto &b : f) n += b.bytes;
     *bytes = n;

@@ -1,0 +1,8 @@
+// Dslash, FP64: instances of dslash_kernel.h.
+#include "dslash_kernel.h"
+
+namespace hisq {
+
+template int launch_epi<F64, F64, F64>(const Geom &g, const DslashLaunch &a, hipStream_t s);
+
+}  // namespace hisq

@@ -1,0 +1,8 @@
+// Dslash, FP16 links on FP32 vectors: instances of dslash_kernel.h.
+#include "dslash_kernel.h"
+
+namespace hisq {
+
+template int launch_epi<H16, F32, F32>(const Geom &g, const DslashLaunch &a, hipStream_t s);
+
+}  // namespace hisq

@@ -1,0 +1,8 @@
+// Shared-link multi-RHS Dslash, FP16S with FP32 output: instances of dslash_shared.h.
+#include "dslash_shared.h"
+
+namespace hisq {
+
+template int launch_shared_fmt<H16, H16, F32>(const Geom &g, const DslashLaunch &a, hipStream_t s);
+
+}  // namespace hisq

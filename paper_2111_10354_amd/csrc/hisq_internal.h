@@ -146,6 +146,35 @@ __host__ __device__ __forceinline__ int tmarch_first_site(const Geom &g, int i, 
     return (i - q * cols) + q * K * cols;
 }
 
+// Order in which the workgroups of a shared launch take the 64-site tiles:
+// order[b] = tile of workgroup b.  The tiles are swept in columns of `by`
+// y-rows by `bz` z-planes along t (a tile belongs to the row of its first
+// site, so any extents will do), and workgroup b, which runs on XCD b % 8, takes the next
+// tile of the b % 8-th eighth of the sweep: the gathers of an XCD's workgroups
+// then share its L2.  On 48^3 x 12 (FP32, 16 right-hand sides, R = W = 4)
+// columns of 4 x 4, 6 x 6, 8 x 8 and 12 x 12 rows take 0.328, 0.327, 0.329 and
+// 0.339 ms, whole planes 0.383 ms, memory order 0.45 ms.
+constexpr int kTileColumn = 864;  // sites of a column's t-slice: 6 x 6 rows of 24
+inline void link_tile_order(const Geom &g, int *order) {
+    const int Ly = g.L[1], Lz = g.L[2], Lt = g.L[3], ntiles = (g.vh + 63) / 64;
+    int side = 1;
+    while ((side + 1) * (side + 1) * g.lxh <= kTileColumn) ++side;
+    int xcd = 0, b = 0;  // next workgroup of the current XCD
+    for (int z0 = 0; z0 < Lz; z0 += side)
+        for (int y0 = 0; y0 < Ly; y0 += side)
+            for (int t = 0; t < Lt; ++t)
+                for (int z = z0; z < z0 + side && z < Lz; ++z)
+                    for (int y = y0; y < y0 + side && y < Ly; ++y) {
+                        const int64_t row = ((int64_t)t * Lz + z) * Ly + y;
+                        const int end = (int)(((row + 1) * g.lxh + 63) / 64);
+                        for (int tile = (int)((row * g.lxh + 63) / 64); tile < end; ++tile) {
+                            order[b] = tile;
+                            b += 8;
+                            if (b >= ntiles) b = ++xcd;
+                        }
+                    }
+}
+
 // ------------------------------------------------------------------ formats
 enum Fmt { F64 = HISQ_PREC_FP64, F32 = HISQ_PREC_FP32, H16 = HISQ_PREC_FP16S };
 
@@ -559,12 +588,31 @@ struct DslashLaunch {
     int order;  // tile processing order: 0 memory order, 1 t-fastest planes,
                 // 2 | BY << 8 | BZ << 16 XCD bricks (dslash.hip); bits 24-25:
                 // log2 of the waves a site's RHS tiles are split over
-    int compressed;  // links in a compressed layout (CompMode)
+    int compressed;    // links in a compressed layout (CompMode)
+    bool cached;       // one RHS per thread: links through the caches, not streamed
+    const int *tiles;  // device, order of the 64-site tiles (link_tile_order); shared shapes only
 };
 int launch_dslash(const Geom &g, const DslashLaunch &a, hipStream_t s);
 bool order_supported(const Geom &g, int order, int block);
 // Workgroups along the sites of a launch with `block` threads and tile order
 // `order` (bits 24-25: the RHS split over waves).
 int dslash_grid_blocks(const Geom &g, int block, int order);
+
+// Shared shapes (dslash_shared.h): order 2 without a column size (BY = BZ = 0),
+// W wavefronts of `tile` right-hand sides each on the same 64 sites, block =
+// 64 W; bits 24-25 of the order are 1, 2 and 3 for W = 2, 4 and 3.
+inline int shared_waves(int order) {
+    if ((order & 0xffffff) != 2) return 0;
+    const int b = (order >> 24) & 3;
+    return b == 1 ? 2 : b == 2 ? 4 : b == 3 ? 3 : 0;
+}
+// the (tile, W) that are built
+inline bool shared_built(int tile, int waves) {
+    return tile == 1 ? waves >= 2 && waves <= 4 : tile == 2 || tile == 3 ? waves == 3 || waves == 4 : tile == 4 && waves == 4;
+}
+inline int shared_order(int waves) { return 2 | (waves == 2 ? 1 : waves == 4 ? 2 : 3) << 24; }
+// The kernel's 32-bit byte offsets reach 2^28 sites of 16 bytes.
+inline bool shared_supported(const Geom &g) { return g.vh < (1 << 28); }
+int launch_dslash_shared(const Geom &g, const DslashLaunch &a, hipStream_t s);
 
 }  // namespace hisq

@@ -38,17 +38,65 @@ size_t dslash_algorithmic_bytes(int fl, int fi, int fo, int64_t vh, int nrhs, bo
     return (size_t)vh * (links + (size_t)nrhs * per_rhs);
 }
 
+// Default launch shapes, by the measured times of the plain Dslash in a loop
+// (us, links cached where links_cached says so):
+//  * Few wavefronts (one per 64 sites and right-hand side, at most one per
+//    SIMD): one right-hand side per thread, all sixteen gathers in flight.  A
+//    shared launch, with its stages, takes longer: 8^4, FP32, 4 RHS 4.6
+//    against 5.6; 16^3 x 8, 4 RHS 5.9 against 6.3.  Not once the copies of the
+//    links that the XCDs fetch for different RHS crowd each other out of the
+//    L2s: 20^3 x 8, FP32, 2 RHS 12.4 against 8.4; 12^3 x 8, FP64, 2 RHS 11.8
+//    against 7.0.
+//  * FP64 from 2, FP32 from 3 and FP16S from 5 right-hand sides: links shared
+//    through LDS, R = ceil(n / 4) per wavefront, at most 16 per workgroup.
+//    48^3 x 12 against the best other shape: FP64 n = 4 355 / 492, n = 16
+//    796 / 1778; FP32 n = 3 147 / 169, n = 8 208 / 278, n = 16 338 / 492;
+//    FP16S n = 5 149 / 178, n = 8 178 / 190, n = 16 320 / 360.
+//  * Fewer: an RHS tile per thread.  FP16S has to convert a link once per
+//    wavefront, which more RHS per thread spread: 48^3 x 12, n = 4 110 (tile 4)
+//    against 127; FP32 n = 2 132 (tile 2) against 138, while a small lattice
+//    gains from twice the wavefronts (24^3 x 8: 12.2 shared, 13.1 tile 2).
 DslashShape pick_shape(hisq_gauge_s *g, int fl, int fi, int fo, int nrhs, bool epi) {
     auto it = g->shapes.find(std::make_tuple(fl, fi, fo, nrhs, (int)epi));
     if (it != g->shapes.end()) return it->second;
     DslashShape s;
-    const int maxt = (fl == F64) ? 4 : 8;
-    s.tile = 1;
-    while (s.tile * 2 <= std::min(nrhs, maxt)) s.tile *= 2;
-    // measured on the 96^3 x 24 FP32 Dslash: 128-thread blocks are best for one RHS
-    s.block = s.tile == 1 ? 128 : 256;
+    const int tiles = (g->geom.vh + 63) / 64;
+    const bool few = (int64_t)tiles * nrhs <= 1024 && tiles <= (fl == F64 ? 64 : fi == H16 ? 1024 : 256);
+    auto plain = [&](int tile, int block) {
+        s.tile = tile;
+        s.block = block;
+    };
+    if (nrhs == 1) {
+        // measured on the 96^3 x 24 FP32 Dslash: 128-thread blocks are best for
+        // one RHS; small lattices need the blocks (8^4, FP64: 5.7 against 5.9)
+        plain(1, tiles < 2048 ? 64 : 128);
+    } else if (few) {
+        plain(1, 64);
+    } else if (fi == H16 && nrhs == 2) {
+        plain(2, 128);
+    } else if (fi == H16 && nrhs == 4) {
+        plain(4, 64);
+    } else if (fi == F32 && nrhs == 2 && tiles >= 2048) {
+        plain(2, 64);
+    } else if (!shared_supported(g->geom)) {
+        const int maxt = (fl == F64) ? 4 : 8;
+        while (s.tile * 2 <= std::min(nrhs, maxt)) s.tile *= 2;
+    } else {
+        const int per = (nrhs + (nrhs + 15) / 16 - 1) / ((nrhs + 15) / 16);  // per workgroup, evenly
+        s.tile = (per + 3) / 4;
+        const int waves = (per + s.tile - 1) / s.tile;
+        s.block = 64 * waves;
+        s.order = shared_order(waves);
+    }
     return s;
 }
+
+// Links of a launch go through the caches where both parities' fit the 256 MiB
+// Infinity Cache, and past them otherwise.  One RHS, links through / past the
+// caches: 12^3 x 8 FP64 5.8 / 12.2 us, 16^3 x 8 FP32 4.8 / 9.2, 24^3 x 8 FP32
+// 11.1 / 13.3, 32^3 x 8 FP32 (241 MiB) 21.0 / 22.0, FP64 (576 MiB) 51.2 / 50.6,
+// 48^3 x 12 FP32 (1.2 GiB) 129 / 119.
+bool links_cached(const hisq_gauge_s *g, int fl) { return g->links[fl][0].bytes <= ((size_t)128 << 20); }
 
 int gauge_dslash(hisq_gauge_s *g, int out_parity, int fl, int fi, int fo, int nrhs, const void *in,
                  void *out, const void *y, const double *diag_dev, double *partials, const CgState *skip,
@@ -76,6 +124,8 @@ int gauge_dslash(hisq_gauge_s *g, int out_parity, int fl, int fi, int fo, int nr
     a.block = sh.block;
     a.order = sh.order;
     a.compressed = links_compressed(g, fl);
+    a.cached = links_cached(g, fl);
+    a.tiles = (const int *)g->tile_order.p;
     return launch_dslash(g->geom, a, s);
 }
 

@@ -159,6 +159,7 @@ struct hisq_gauge_s {
     int device = 0;
     hisq::DevBuf links[3][2];  // [format][output parity]
     int comp_mode = 0;         // CompMode of the FP32 / FP16 long links (two rows + sign bit or kappa)
+    hisq::DevBuf tile_order;   // link_tile_order of the lattice
     hisq::DevBuf diag_buf;     // epilogue coefficients for hisq_dslash_multi_rhs
     hipEvent_t diag_event = nullptr;  // recorded after the last kernel that read diag_buf
     hisq::DevBuf thin;         // thin links (FP16) for the preconditioner network
@@ -186,6 +187,7 @@ inline int sloppy_vec_fmt(int sloppy) { return sloppy == HISQ_PREC_FP16L ? F32 :
 inline int links_compressed(const hisq_gauge_s *g, int fmt) { return fmt == F64 ? COMP_NONE : g->comp_mode; }
 
 DslashShape pick_shape(hisq_gauge_s *g, int fl, int fi, int fo, int nrhs, bool epi);
+bool links_cached(const hisq_gauge_s *g, int fl);
 
 // Argument checks shared by the multi-RHS Dslash entry points (HISQ_OK or an
 // error code with the message set).
