@@ -312,11 +312,15 @@ __device__ __forceinline__ void transport_chunk(int q, const Lex &g, const void 
 // amat: bf16 [16][kp_of(INM)], rows 0..7 Re and 8..15 Im of the output
 // channels.  OUTM == IO_FULL: all V sites, output BF16 hidden units;
 // IO_EVEN: even sites in checkerboard order, output channel 0 as an FP32
-// public spinor.
+// public spinor.  One grid row per sample, `in` and `out` of sample y `in_step`
+// and `out_step` bytes on from those of the sample before.
 template <int INM, int OUTM>
-__global__ __launch_bounds__(64 * NN_WAVES) void k_nn_layer(Lex g, const void *thin, const void *__restrict__ in,
-                                                            void *__restrict__ out, const __bf16 *__restrict__ amat) {
+__global__ __launch_bounds__(64 * NN_WAVES) void k_nn_layer(Lex g, const void *thin, const void *__restrict__ in0,
+                                                            void *__restrict__ out0, const __bf16 *__restrict__ amat,
+                                                            size_t in_step, size_t out_step) {
     constexpr int KP = kp_of(INM);
+    const void *__restrict__ in = (const char *)in0 + in_step * blockIdx.y;
+    void *__restrict__ out = (char *)out0 + out_step * blockIdx.y;
     __shared__ __attribute__((aligned(16))) __bf16 Bt[NN_WAVES][NW_COLS][BT_LD];
     __shared__ float Of[NN_WAVES][NW_SITES][6];
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, j = l >> 4;
@@ -386,10 +390,13 @@ __global__ __launch_bounds__(64 * NN_WAVES) void k_nn_layer(Lex g, const void *t
 // r < 8: Re(g_r conj t_n), r >= 8: Im(g_{r-8} conj t_n).  The upstream gradient
 // g has mode GM (IO_FULL: BF16 hidden units on all sites; IO_EVEN: channel 0
 // as an FP32 public spinor on even sites); sites are enumerated like the
-// layer kernel with OUTM = GM.
+// layer kernel with OUTM = GM.  One grid row per sample, as in the layer kernel.
 template <int INM, int GM>
-__global__ __launch_bounds__(64 * NN_WAVES) void k_nn_wgrad(Lex g, const void *thin, const void *__restrict__ in,
-                                                            const void *__restrict__ grad, float *__restrict__ partial) {
+__global__ __launch_bounds__(64 * NN_WAVES) void k_nn_wgrad(Lex g, const void *thin, const void *__restrict__ in0,
+                                                            const void *__restrict__ grad0, float *__restrict__ partial,
+                                                            size_t in_step, size_t grad_step) {
+    const void *__restrict__ in = (const char *)in0 + in_step * blockIdx.y;
+    const void *__restrict__ grad = (const char *)grad0 + grad_step * blockIdx.y;
     constexpr int KP = kp_of(INM);
     constexpr int NQ = KP / 32;  // chunks
     constexpr int KC = INM == IO_EVEN ? 16 : 80;
@@ -477,41 +484,62 @@ __global__ __launch_bounds__(64 * NN_WAVES) void k_nn_wgrad(Lex g, const void *t
         const int r = e / KC, k = e % KC;
         float s = 0.f;
         for (int ww = 0; ww < NN_WAVES; ++ww) s += Red[ww][r][k];
-        partial[(size_t)blockIdx.x * 16 * KC + e] = s;
+        partial[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 16 * KC + e] = s;
     }
 }
 
-// Two-stage fixed-order sum of the block partials.  Stage 1: segment sg of
-// the blocks, every entry e of the 16 x KC partial: fold[sg][e].
+// Three-stage fixed-order sum of the block partials.  Stage 1: segment sg of
+// sample z's blocks, every entry e of the 16 x KC partial: fold[z][sg][e].
 constexpr int NN_FOLD = 64;  // segments
 
 __global__ __launch_bounds__(256) void k_nn_wgrad_fold(const float *__restrict__ partial, int nblk, int nent,
                                                       float *__restrict__ fold) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x, sg = blockIdx.y;
     if (e >= nent) return;
+    partial += (size_t)blockIdx.z * nblk * nent;
     const int per = (nblk + NN_FOLD - 1) / NN_FOLD;
     const int b0 = sg * per, b1 = min(nblk, b0 + per);
     float s = 0.f;
     for (int b = b0; b < b1; ++b) s += partial[(size_t)b * nent + e];
-    fold[(size_t)sg * nent + e] = s;
+    fold[((size_t)blockIdx.z * NN_FOLD + sg) * nent + e] = s;
 }
 
-// Stage 2: grad[p][a][b] (complex double) += sum over the segments (fixed order).
-__global__ void k_nn_wgrad_reduce(const float *__restrict__ fold, int inm, int cin, int cout, double *grad) {
+// Stage 2: the layer's part of sample y's gradient, [p][a][b] (complex double)
+// = sum over the segments (fixed order); `step` doubles from sample to sample.
+__global__ void k_nn_wgrad_reduce(const float *__restrict__ fold, int inm, int cin, int cout, double *red,
+                                  size_t step) {
     const int KC = inm == IO_EVEN ? 16 : 80;
     const int e = blockIdx.x * blockDim.x + threadIdx.x;  // (a, p, b)
     if (e >= cout * 9 * cin) return;
     const int a = e / (9 * cin), pb = e % (9 * cin), p = pb / cin, b = pb % cin;
     const int n = inm == IO_EVEN ? p : 8 * p + b;
+    fold += (size_t)blockIdx.y * NN_FOLD * 16 * KC;
     double re = 0.0, im = 0.0;
+#pragma unroll 16
     for (int sg = 0; sg < NN_FOLD; ++sg) {
         const float *P = fold + (size_t)sg * 16 * KC;
         re += P[a * KC + n];
         im += P[(8 + a) * KC + n];
     }
-    double *gp = grad + 2 * (((size_t)p * cout + a) * cin + b);
-    gp[0] += re;
-    gp[1] += im;
+    double *gp = red + step * blockIdx.y + 2 * (((size_t)p * cout + a) * cin + b);
+    gp[0] = re;
+    gp[1] = im;
+}
+
+// Stage 3, all weights: grad += the samples' gradients, one after another;
+// thread n adds the samples' losses (scal[8 z + 3]) to *loss the same way.
+__global__ void k_nn_grad_add(const double *__restrict__ red, int n, int samples, double *__restrict__ grad,
+                              const double *__restrict__ scal, double *loss) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) {
+        double s = grad[i];
+        for (int z = 0; z < samples; ++z) s += red[(size_t)z * n + i];
+        grad[i] = s;
+    } else if (i == n) {
+        double s = *loss;
+        for (int z = 0; z < samples; ++z) s += scal[8 * z + 3];
+        *loss = s;
+    }
 }
 
 // Real-block bf16 matrix of a layer (transposed = the adjoint layer), in the
@@ -555,37 +583,38 @@ __global__ void k_nn_build_amat(const double *__restrict__ W, int cin, int cout,
     amat[e] = (__bf16)(float)val;
 }
 
-// loss pieces on even sites, one sample: partial |out - v|^2 and G(out) = scale (out - v)
-__global__ __launch_bounds__(256) void k_nn_loss_grad(Spinor<F32> out, Spinor<F32> v, const double *__restrict__ scale,
+// loss pieces on even sites, one grid row per sample: partial |out - v|^2 and
+// G(out) = scale (out - v)
+__global__ __launch_bounds__(256) void k_nn_loss_grad(Spinor<F32> out, Spinor<F32> v, const double *__restrict__ scal,
                                                       Spinor<F32> gout, double *__restrict__ part) {
-    const int h = blockIdx.x * blockDim.x + threadIdx.x;
+    const int h = blockIdx.x * blockDim.x + threadIdx.x, z = blockIdx.y;
     double dd = 0.0;
     if (h < v.vh) {
         cx<float> o[3], t[3], gg[3];
-        out.load(h, o);
-        v.load(h, t);
-        const float sc = (float)scale[0];
+        out.rhs(z).load(h, o);
+        v.rhs(z).load(h, t);
+        const float sc = (float)scal[8 * z + 1];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const float dr = o[c].re - t[c].re, di = o[c].im - t[c].im;
             dd += (double)dr * dr + (double)di * di;
             gg[c] = {sc * dr, sc * di};
         }
-        gout.store(h, gg);
+        gout.rhs(z).store(h, gg);
     }
     __shared__ double red[4];
     for (int off = 32; off >= 1; off >>= 1) dd += __shfl_xor(dd, off, 64);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = dd;
     __syncthreads();
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+    if (threadIdx.x == 0) part[(size_t)z * gridDim.x + blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
 
 __global__ __launch_bounds__(256) void k_nn_norm2(Spinor<F32> v, double *__restrict__ part) {
-    const int h = blockIdx.x * blockDim.x + threadIdx.x;
+    const int h = blockIdx.x * blockDim.x + threadIdx.x, z = blockIdx.y;
     double dd = 0.0;
     if (h < v.vh) {
         cx<float> t[3];
-        v.load(h, t);
+        v.rhs(z).load(h, t);
 #pragma unroll
         for (int c = 0; c < 3; ++c) dd += (double)t[c].re * t[c].re + (double)t[c].im * t[c].im;
     }
@@ -593,13 +622,16 @@ __global__ __launch_bounds__(256) void k_nn_norm2(Spinor<F32> v, double *__restr
     for (int off = 32; off >= 1; off >>= 1) dd += __shfl_xor(dd, off, 64);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = dd;
     __syncthreads();
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+    if (threadIdx.x == 0) part[(size_t)z * gridDim.x + blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
 
-// s[0] = sum of partials (fixed order); mode 0: scale = 2 / (B |v|^2) into s[1], keep |v|^2 in s[2]
-// mode 1: loss += sum / (|v|^2 B)
-__global__ void k_nn_scalar(const double *__restrict__ part, int n, double *s, int mode, int batch) {
+// Sample z's scalars s = scal + 8 z from the sum of its n partials (fixed
+// order); mode 0: scale = 2 / (B |v|^2) into s[1], keep |v|^2 in s[2];
+// mode 1: its part of the loss, sum / (|v|^2 B), into s[3]
+__global__ void k_nn_scalar(const double *__restrict__ part, int n, double *scal, int mode, int batch) {
     __shared__ double red[256];
+    double *s = scal + 8 * blockIdx.x;
+    part += (size_t)blockIdx.x * n;
     double acc = 0.0;
     for (int i = threadIdx.x; i < n; i += blockDim.x) acc += part[i];
     red[threadIdx.x] = acc;
@@ -611,7 +643,7 @@ __global__ void k_nn_scalar(const double *__restrict__ part, int n, double *s, i
             s[2] = t;
             s[1] = t > 0.0 ? 2.0 / ((double)batch * t) : 0.0;
         } else {
-            s[3] += s[2] > 0.0 ? t / (s[2] * (double)batch) : 0.0;
+            s[3] = s[2] > 0.0 ? t / (s[2] * (double)batch) : 0.0;
         }
     }
 }
@@ -645,42 +677,50 @@ size_t nn_wgrad_partial_floats(const NnGeom &G) { return ((size_t)grid_blocks(G.
 size_t nn_thin_bytes(const NnGeom &G) { return (size_t)((G.V + 63) / 64) * 9 * 1024 + 256; }
 
 int nn_layer(const NnGeom &G, const void *thin, int inm, int outm, const void *in, void *out, const void *amat,
-             hipStream_t s) {
+             int samples, size_t in_step, size_t out_step, hipStream_t s) {
     const Lex L = lex_of(G);
-    const dim3 grid(grid_blocks(outm == IO_FULL ? G.V : G.V / 2)), block(64 * NN_WAVES);
+    const dim3 grid(grid_blocks(outm == IO_FULL ? G.V : G.V / 2), samples), block(64 * NN_WAVES);
     const __bf16 *A = (const __bf16 *)amat;
     if (inm == IO_FULL && outm == IO_FULL)
-        hipLaunchKernelGGL((k_nn_layer<IO_FULL, IO_FULL>), grid, block, 0, s, L, thin, in, out, A);
+        hipLaunchKernelGGL((k_nn_layer<IO_FULL, IO_FULL>), grid, block, 0, s, L, thin, in, out, A, in_step, out_step);
     else if (inm == IO_EVEN && outm == IO_FULL)
-        hipLaunchKernelGGL((k_nn_layer<IO_EVEN, IO_FULL>), grid, block, 0, s, L, thin, in, out, A);
+        hipLaunchKernelGGL((k_nn_layer<IO_EVEN, IO_FULL>), grid, block, 0, s, L, thin, in, out, A, in_step, out_step);
     else if (inm == IO_FULL && outm == IO_EVEN)
-        hipLaunchKernelGGL((k_nn_layer<IO_FULL, IO_EVEN>), grid, block, 0, s, L, thin, in, out, A);
+        hipLaunchKernelGGL((k_nn_layer<IO_FULL, IO_EVEN>), grid, block, 0, s, L, thin, in, out, A, in_step, out_step);
     else
-        hipLaunchKernelGGL((k_nn_layer<IO_EVEN, IO_EVEN>), grid, block, 0, s, L, thin, in, out, A);
+        hipLaunchKernelGGL((k_nn_layer<IO_EVEN, IO_EVEN>), grid, block, 0, s, L, thin, in, out, A, in_step, out_step);
     HISQ_HIP_CHECK(hipGetLastError());
     return HISQ_OK;
 }
 
 int nn_wgrad(const NnGeom &G, const void *thin, int cin, int cout, int inm, int gm, const void *in, const void *grad,
-             float *partial, double *gacc, hipStream_t s) {
+             int samples, size_t in_step, size_t grad_step, float *partial, double *red, size_t red_step,
+             hipStream_t s) {
     const Lex L = lex_of(G);
     const int nblk = grid_blocks(gm == IO_FULL ? G.V : G.V / 2);
-    const dim3 grid(nblk), block(64 * NN_WAVES);
+    const dim3 grid(nblk, samples), block(64 * NN_WAVES);
     if (inm == IO_FULL && gm == IO_FULL)
-        hipLaunchKernelGGL((k_nn_wgrad<IO_FULL, IO_FULL>), grid, block, 0, s, L, thin, in, grad, partial);
+        hipLaunchKernelGGL((k_nn_wgrad<IO_FULL, IO_FULL>), grid, block, 0, s, L, thin, in, grad, partial, in_step, grad_step);
     else if (inm == IO_EVEN && gm == IO_FULL)
-        hipLaunchKernelGGL((k_nn_wgrad<IO_EVEN, IO_FULL>), grid, block, 0, s, L, thin, in, grad, partial);
+        hipLaunchKernelGGL((k_nn_wgrad<IO_EVEN, IO_FULL>), grid, block, 0, s, L, thin, in, grad, partial, in_step, grad_step);
     else if (inm == IO_FULL && gm == IO_EVEN)
-        hipLaunchKernelGGL((k_nn_wgrad<IO_FULL, IO_EVEN>), grid, block, 0, s, L, thin, in, grad, partial);
+        hipLaunchKernelGGL((k_nn_wgrad<IO_FULL, IO_EVEN>), grid, block, 0, s, L, thin, in, grad, partial, in_step, grad_step);
     else
-        hipLaunchKernelGGL((k_nn_wgrad<IO_EVEN, IO_EVEN>), grid, block, 0, s, L, thin, in, grad, partial);
+        hipLaunchKernelGGL((k_nn_wgrad<IO_EVEN, IO_EVEN>), grid, block, 0, s, L, thin, in, grad, partial, in_step, grad_step);
     const int nent = 16 * (inm == IO_EVEN ? 16 : 80);
-    float *fold = partial + (size_t)grid_blocks(G.V) * 16 * 80;
-    hipLaunchKernelGGL(k_nn_wgrad_fold, dim3((nent + 255) / 256, NN_FOLD), dim3(256), 0, s, partial, nblk, nent, fold);
+    float *fold = partial + (size_t)samples * grid_blocks(G.V) * 16 * 80;
+    hipLaunchKernelGGL(k_nn_wgrad_fold, dim3((nent + 255) / 256, NN_FOLD, samples), dim3(256), 0, s, partial, nblk,
+                       nent, fold);
     const int n = cout * 9 * cin;
-    hipLaunchKernelGGL(k_nn_wgrad_reduce, dim3((n + 127) / 128), dim3(128), 0, s, fold, inm, cin, cout, gacc);
+    hipLaunchKernelGGL(k_nn_wgrad_reduce, dim3((n + 63) / 64, samples), dim3(64), 0, s, fold, inm, cin, cout, red,
+                       red_step);
     HISQ_HIP_CHECK(hipGetLastError());
     return HISQ_OK;
+}
+
+void nn_grad_add(const double *red, int n, int samples, double *grad, const double *scal, double *loss,
+                 hipStream_t s) {
+    hipLaunchKernelGGL(k_nn_grad_add, dim3((n + 1 + 255) / 256), dim3(256), 0, s, red, n, samples, grad, scal, loss);
 }
 
 void nn_build_amat(const double *W, int cin, int cout, bool transposed, int inm, void *amat, hipStream_t s) {
@@ -705,14 +745,15 @@ int nn_pack_thin(const NnGeom &G, const double *U, void *dst, hipStream_t s) {
     return HISQ_OK;
 }
 
-void nn_loss_grad(int vh, const float *out, const float *v, float *gout, double *part, double *scal, int batch,
-                  hipStream_t s) {
+void nn_loss_grad(int vh, int samples, const float *out, const float *v, float *gout, double *part, double *scal,
+                  int batch, hipStream_t s) {
     const int nb = (vh + 255) / 256;
+    const dim3 grid(nb, samples);
     Spinor<F32> O{const_cast<float *>(out), vh}, T{const_cast<float *>(v), vh}, Gg{gout, vh};
-    hipLaunchKernelGGL(k_nn_norm2, dim3(nb), dim3(256), 0, s, T, part);
-    hipLaunchKernelGGL(k_nn_scalar, dim3(1), dim3(256), 0, s, part, nb, scal, 0, batch);
-    hipLaunchKernelGGL(k_nn_loss_grad, dim3(nb), dim3(256), 0, s, O, T, scal + 1, Gg, part);
-    hipLaunchKernelGGL(k_nn_scalar, dim3(1), dim3(256), 0, s, part, nb, scal, 1, batch);
+    hipLaunchKernelGGL(k_nn_norm2, grid, dim3(256), 0, s, T, part);
+    hipLaunchKernelGGL(k_nn_scalar, dim3(samples), dim3(256), 0, s, part, nb, scal, 0, batch);
+    hipLaunchKernelGGL(k_nn_loss_grad, grid, dim3(256), 0, s, O, T, scal, Gg, part);
+    hipLaunchKernelGGL(k_nn_scalar, dim3(samples), dim3(256), 0, s, part, nb, scal, 1, batch);
 }
 
 void nn_adam(double *w, double *m, double *v, const double *g, int n, double lr, int step, hipStream_t s) {

@@ -21,6 +21,36 @@ static NnGeom nn_geom(const hisq_gauge_s *g) {
 // one-channel even-site spinor, every other layer a hidden activation
 enum { MODE_HIDDEN = 0, MODE_EVEN = 1 };
 
+// Device buffers for `cap` training samples side by side; the old ones stay if
+// there is no memory for them (HISQ_ERR_OOM).
+static int train_alloc(hisq_nn_s *n, int cap) {
+    const NnGeom G = nn_geom(n->gauge);
+    const size_t act = nn_act_bytes(G), sb = spinor_bytes(F32, G.V / 2);
+    hisq_nn_s::Train &t = n->train;
+    t.cap = 0;
+    for (DevBuf *b : {&t.act, &t.gbuf, &t.out, &t.gout, &t.partial, &t.red, &t.scal, &t.partd}) b->release();
+    int rc;
+    if ((rc = t.act.alloc(std::max<size_t>((n->nlayers - 1) * act * cap, 16))) || (rc = t.gbuf.alloc(2 * act * cap)) ||
+        (rc = t.out.alloc(sb * cap)) || (rc = t.gout.alloc(sb * cap)) ||
+        (rc = t.partial.alloc(nn_wgrad_partial_floats(G) * 4 * cap)) || (rc = t.red.alloc(n->nweights * 8 * cap)) ||
+        (rc = t.scal.alloc(8 * sizeof(double) * cap)) ||
+        (rc = t.partd.alloc(sizeof(double) * ((G.V / 2 + 255) / 256 + 1) * cap)))
+        return rc;
+    t.cap = cap;
+    return HISQ_OK;
+}
+
+// Samples that go through the layers together: all of the batch, within 512 MiB
+// of buffers.  A sample's layer on 16^3 x 8 has one wavefront per SIMD and its
+// reductions are 13 launches: 8 samples one by one 1.12 ms.  From 32^3 x 8 on
+// one sample fills the card and the limit (4 samples there) costs nothing.
+static int train_group(const hisq_nn_s *n, int batch) {
+    const NnGeom G = nn_geom(n->gauge);
+    const size_t one = (size_t)(n->nlayers + 1) * nn_act_bytes(G) + 2 * spinor_bytes(F32, G.V / 2) +
+                       nn_wgrad_partial_floats(G) * 4;
+    return (int)std::max<size_t>(1, std::min<size_t>(batch, ((size_t)512 << 20) / one));
+}
+
 int nn_create(hisq_nn_s **out, hisq_gauge_s *g, int nlayers, const int *ch, const double *weights, hipStream_t s) {
     static std::atomic<unsigned long long> next_id{1};
     hisq_nn_s *n = new (std::nothrow) hisq_nn_s();
@@ -44,16 +74,13 @@ int nn_create(hisq_nn_s **out, hisq_gauge_s *g, int nlayers, const int *ch, cons
         aoff_t += nn_amat_elems(l == nlayers - 1 ? MODE_EVEN : MODE_HIDDEN);
     }
     const size_t act = (size_t)(nlayers - 1) * nn_act_bytes(G);
-    const size_t part = nn_wgrad_partial_floats(G);
     n->aoff.insert(n->aoff.end(), aoff_tv.begin(), aoff_tv.end());  // [fwd offsets..., adjoint offsets...]
     n->nweights = off;
     int rc;
     if ((rc = n->w.alloc(off * 8)) || (rc = n->m.alloc(off * 8)) || (rc = n->v.alloc(off * 8)) ||
         (rc = n->g.alloc(off * 8)) || (rc = n->amat.alloc(aoff * 2)) || (rc = n->amat_t.alloc(aoff_t * 2)) ||
-        (rc = n->act.alloc(std::max<size_t>(act, 16))) || (rc = n->gbuf.alloc(2 * nn_act_bytes(G))) ||
-        (rc = n->out.alloc(spinor_bytes(F32, G.V / 2))) || (rc = n->gout.alloc(spinor_bytes(F32, G.V / 2))) ||
-        (rc = n->partial.alloc(part * 4)) || (rc = n->scal.alloc(8 * sizeof(double))) ||
-        (rc = n->partd.alloc(sizeof(double) * ((G.V / 2 + 255) / 256 + 1)))) {
+        (rc = n->act.alloc(std::max<size_t>(act, 16))) || (rc = n->scal.alloc(8 * sizeof(double))) ||
+        (rc = train_alloc(n, 1))) {
         delete n;
         return rc;
     }
@@ -97,45 +124,68 @@ int nn_forward(hisq_nn_s *n, const float *in, float *out, hipStream_t s) {
         const void *src = l == 0 ? (const void *)in : act_of(n, l);
         void *dst = l == L - 1 ? (void *)out : act_of(n, l + 1);
         const int inm = l == 0 ? MODE_EVEN : MODE_HIDDEN, outm = l == L - 1 ? MODE_EVEN : MODE_HIDDEN;
-        if ((rc = nn_layer(G, g->thin.p, inm, outm, src, dst, (const __bf16 *)n->amat.p + n->aoff[l], s))) return rc;
+        if ((rc = nn_layer(G, g->thin.p, inm, outm, src, dst, (const __bf16 *)n->amat.p + n->aoff[l], 1, 0, 0, s)))
+            return rc;
     }
     return HISQ_OK;
 }
 
 // Loss over a batch and its gradient, accumulated into n->g (overwritten);
-// the loss ends in scal[3].
+// the loss ends in scal[3].  The samples go through the layers in groups; each
+// sample's sums are its own, and samples are added in order, so the result
+// does not depend on the grouping.
 int nn_loss_grad_batch(hisq_nn_s *n, int batch, const float *av, const float *v, hipStream_t s) {
     hisq_gauge_s *g = n->gauge;
     const NnGeom G = nn_geom(g);
     const int vh = G.V / 2, L = n->nlayers;
-    const size_t sb = spinor_bytes(F32, vh);
+    const size_t sb = spinor_bytes(F32, vh), act = nn_act_bytes(G);
     int rc;
+    const int want = train_group(n, batch);
+    if (want > n->train.cap) {
+        rc = train_alloc(n, want);
+        if (rc == HISQ_ERR_OOM) rc = train_alloc(n, 1);
+        if (rc) return rc;
+    }
     HISQ_HIP_CHECK(hipMemsetAsync(n->g.p, 0, n->nweights * 8, s));
     HISQ_HIP_CHECK(hipMemsetAsync(n->scal.p, 0, 8 * sizeof(double), s));
-    void *gb[2] = {n->gbuf.p, (char *)n->gbuf.p + nn_act_bytes(G)};
-    for (int i = 0; i < batch; ++i) {
-        const float *avi = (const float *)((const char *)av + sb * i);
-        const float *vi = (const float *)((const char *)v + sb * i);
-        if ((rc = nn_forward(n, avi, (float *)n->out.p, s))) return rc;
-        nn_loss_grad(vh, (const float *)n->out.p, vi, (float *)n->gout.p, (double *)n->partd.p, (double *)n->scal.p,
+    if (!n->amat_valid) build_amats(n, s);
+    hisq_nn_s::Train &t = n->train;
+    for (int first = 0; first < batch; first += t.cap) {
+        const int m = std::min(t.cap, batch - first);
+        const float *avi = (const float *)((const char *)av + sb * first);
+        const float *vi = (const float *)((const char *)v + sb * first);
+        auto hidden = [&](int l) { return (char *)t.act.p + (size_t)(l - 1) * t.cap * act; };  // input of layer l
+        for (int l = 0; l < L; ++l) {
+            const bool first_l = l == 0, last_l = l == L - 1;
+            if ((rc = nn_layer(G, g->thin.p, first_l ? MODE_EVEN : MODE_HIDDEN, last_l ? MODE_EVEN : MODE_HIDDEN,
+                               first_l ? (const void *)avi : hidden(l), last_l ? t.out.p : (void *)hidden(l + 1),
+                               (const __bf16 *)n->amat.p + n->aoff[l], m, first_l ? sb : act, last_l ? sb : act, s)))
+                return rc;
+        }
+        nn_loss_grad(vh, m, (const float *)t.out.p, vi, (float *)t.gout.p, (double *)t.partd.p, (double *)t.scal.p,
                      batch, s);
-        const void *gcur = n->gout.p;
+        void *gb[2] = {t.gbuf.p, (char *)t.gbuf.p + act * t.cap};
+        const void *gcur = t.gout.p;
         int gmode = MODE_EVEN;
         for (int l = L - 1; l >= 0; --l) {
-            const void *inl = l == 0 ? (const void *)avi : act_of(n, l);
+            const void *inl = l == 0 ? (const void *)avi : hidden(l);
             const int inm = l == 0 ? MODE_EVEN : MODE_HIDDEN;
-            if ((rc = nn_wgrad(G, g->thin.p, n->ch[l], n->ch[l + 1], inm, gmode, inl, gcur, (float *)n->partial.p,
-                               (double *)n->g.p + n->woff[l], s)))
+            const size_t gstep = gmode == MODE_EVEN ? sb : act;
+            if ((rc = nn_wgrad(G, g->thin.p, n->ch[l], n->ch[l + 1], inm, gmode, inl, gcur, m, l == 0 ? sb : act, gstep,
+                               (float *)t.partial.p, (double *)t.red.p + n->woff[l], n->nweights, s)))
                 return rc;
             if (l > 0) {
                 void *gn = gb[l & 1];
                 if ((rc = nn_layer(G, g->thin.p, gmode, MODE_HIDDEN, gcur, gn,
-                                   (const __bf16 *)n->amat_t.p + n->aoff[L + l], s)))
+                                   (const __bf16 *)n->amat_t.p + n->aoff[L + l], m, gstep, act, s)))
                     return rc;
                 gcur = gn;
                 gmode = MODE_HIDDEN;
             }
         }
+        nn_grad_add((const double *)t.red.p, (int)n->nweights, m, (double *)n->g.p, (const double *)t.scal.p,
+                    (double *)n->scal.p + 3, s);
+        HISQ_HIP_CHECK(hipGetLastError());
     }
     return HISQ_OK;
 }
