@@ -7,40 +7,10 @@
 // right-hand side; the per-block partial sums are reduced by a single block
 // per RHS in a fixed order, so results are bitwise reproducible.
 
-#include "solver_internal.h"
+#include "reduce.h"
 
 namespace hisq {
 
-template <class T>
-__device__ __forceinline__ T wave_sum64(T v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
-// Sum of one double per thread over the block, in a fixed order; valid in thread 0.
-__device__ __forceinline__ double block_sum(double v) {
-    __shared__ double red[16];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    v = wave_sum64(v);
-    if (lane == 0) red[wv] = v;
-    __syncthreads();
-    double s = 0.0;
-    if (threadIdx.x == 0)
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += red[w];
-    __syncthreads();
-    return s;
-}
-
-__device__ __forceinline__ double reduce_partials(const double *part, int nb) {
-    double s = 0.0;
-    for (int i = threadIdx.x; i < nb; i += blockDim.x) s += part[i];
-    return block_sum(s);
-}
-
-__device__ __forceinline__ bool finite(double v) { return v == v && fabs(v) <= 1.7e308; }
-
-// ---------------------------------------------------------------- scalar steps
 // alpha_i = rho_i / Re<p_i, A p_i>
 __global__ void k_reduce_alpha(const double *__restrict__ part, int nb, CgState *st) {
     const int r = blockIdx.x;
@@ -50,40 +20,15 @@ __global__ void k_reduce_alpha(const double *__restrict__ part, int nb, CgState 
         return;
     }
     const double pap = reduce_partials(part + (size_t)r * nb, nb);
-    if (threadIdx.x == 0) {
-        S.pap = pap;
-        if (!(pap > 0.0) || !finite(pap)) {
-            S.flag = CG_BREAKDOWN;
-            S.xpend = 0;
-        } else {
-            S.alpha = S.rho / pap;
-            S.xpend = 1;
-        }
-    }
+    if (threadIdx.x == 0) alpha_step(S, pap);
 }
 
-// rho_new = |r|^2; decide: continue (beta), convergence check / reliable
-// update due (host attention), or stop at the iteration cap.
 __global__ void k_reduce_beta(const double *__restrict__ part, int nb, CgState *st) {
     const int r = blockIdx.x;
     CgState &S = st[r];
     if (S.flag != CG_RUNNING) return;
     const double rr = reduce_partials(part + (size_t)r * nb, nb);
-    if (threadIdx.x == 0) {
-        S.rho_new = rr;
-        S.iter += 1;
-        S.since_ru += 1;
-        if (!finite(rr)) {
-            S.flag = CG_BREAKDOWN;
-        } else if (rr <= S.stop2 || (S.ru_period > 0 && S.since_ru >= S.ru_period) || rr <= S.ru_delta2 * S.ru_rho) {
-            S.flag = CG_ATTENTION;
-        } else if (S.iter >= S.max_iter) {
-            S.flag = CG_ATTENTION;
-        } else {
-            S.beta = rr / S.rho;
-            S.rho = rr;
-        }
-    }
+    if (threadIdx.x == 0) beta_step(S, rr);
 }
 
 // After a reliable update: rho_true = |b - A x|^2.  mode 0: stop if below the

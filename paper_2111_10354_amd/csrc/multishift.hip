@@ -20,7 +20,7 @@
 #include <cstdlib>
 #include <cstring>
 
-#include "solver_internal.h"
+#include "reduce.h"
 
 namespace hisq {
 
@@ -45,48 +45,74 @@ struct MsGlobal {
 // stacks are shift-major, slot k * nsrc + j (so the sources' base vectors,
 // k = 0, are one contiguous multi-RHS stack).
 
-// after alpha: new zeta and alpha_k for every active shift
-__global__ void k_ms_alpha(const CgState *__restrict__ base_, MsState *ms_, MsGlobal *gl_, int nshift) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x, j = blockIdx.y;
-    const CgState *base = base_ + j;
-    MsGlobal *gl = gl_ + j;
-    if (k == 0 || k >= nshift || base->flag != CG_RUNNING) return;
-    MsState &S = ms_[(size_t)j * nshift + k];
+// after alpha: new zeta and alpha_k of shift k
+__device__ __forceinline__ void ms_alpha(const CgState &base, MsState &S, const MsGlobal &gl) {
     if (S.stop_next) S.active = 0;
     if (!S.active) return;
-    const double a = base->alpha, ao = gl->alpha_old, bo = gl->beta_old;
+    const double a = base.alpha, ao = gl.alpha_old, bo = gl.beta_old;
     const double den = a * bo * (S.zeta_old - S.zeta) + S.zeta_old * ao * (1.0 + a * S.delta);
     S.zeta_new = S.zeta * S.zeta_old * ao / den;
     S.alpha = a * S.zeta_new / S.zeta;
     S.pending = 1;
 }
 
-// after beta: beta_k, roll the zetas, convergence of each shift (base flag ==
-// when); one block per source
+// after beta: beta_k, roll the zetas, convergence of shift k
+__device__ __forceinline__ void ms_beta(const CgState &base, MsState &S, const MsGlobal &gl) {
+    if (!S.active) return;
+    const double ratio = S.zeta_new / S.zeta;
+    S.beta = base.beta * ratio * ratio;
+    S.zeta_old = S.zeta;
+    S.zeta = S.zeta_new;
+    S.iters += 1;
+    if (fabs(S.zeta) * sqrt(base.rho_new) <= gl.stop) S.stop_next = 1;
+}
+
+// The scalars of one iteration between its two vector passes, one block per
+// source: rho' = |r|^2 and beta of the base system, then alpha_k of every shift
+// and, unless the host has to act first, beta_k.  The vector pass that follows
+// applies alpha_k, so it is not pending.
+__global__ __launch_bounds__(256) void k_ms_scalars(const double *__restrict__ part, int nb, CgState *base_,
+                                                    MsState *ms_, MsGlobal *gl_, int nshift) {
+    const int j = blockIdx.x;
+    CgState base = base_[j];
+    if (base.flag != CG_RUNNING) return;
+    beta_step(base, reduce_partials_all(part + (size_t)j * nb, nb));  // every thread has read base_[j]
+    if (threadIdx.x == 0) base_[j] = base;
+    const MsGlobal gl = gl_[j];
+    const bool runs = base.flag == CG_RUNNING;
+    for (int k = threadIdx.x; k < nshift; k += blockDim.x) {
+        if (k == 0) continue;
+        MsState S = ms_[(size_t)j * nshift + k];
+        ms_alpha(base, S, gl);
+        if (runs) {
+            ms_beta(base, S, gl);
+            S.pending = 0;
+        }
+        ms_[(size_t)j * nshift + k] = S;
+    }
+    __syncthreads();  // gl has been read
+    if (runs && threadIdx.x == 0) {
+        gl_[j].alpha_old = base.alpha;
+        gl_[j].beta_old = base.beta;
+    }
+}
+
+// After a reliable update (base flag == when): beta_k of every shift
 __global__ void k_ms_beta(const CgState *__restrict__ base_, MsState *ms_, MsGlobal *gl_, int nshift, int when) {
     const int j = blockIdx.y;
     const CgState *base = base_ + j;
     MsGlobal *gl = gl_ + j;
     if (base->flag != when) return;
-    for (int k = threadIdx.x; k < nshift; k += blockDim.x) {
-        if (k == 0) continue;
-        MsState &S = ms_[(size_t)j * nshift + k];
-        if (S.active) {
-            const double ratio = S.zeta_new / S.zeta;
-            S.beta = base->beta * ratio * ratio;
-            S.zeta_old = S.zeta;
-            S.zeta = S.zeta_new;
-            S.iters += 1;
-            if (fabs(S.zeta) * sqrt(base->rho_new) <= gl->stop) S.stop_next = 1;
-        }
-    }
+    for (int k = threadIdx.x; k < nshift; k += blockDim.x)
+        if (k > 0) ms_beta(*base, ms_[(size_t)j * nshift + k], *gl);
     if (threadIdx.x == 0) {
         gl->alpha_old = base->alpha;
         gl->beta_old = base->beta;
     }
 }
 
-// x_k += alpha_k p_k ; p_k = zeta_k r + beta_k p_k   for every active shift, r read once
+// x_k += alpha_k p_k ; p_k = zeta_k r + beta_k p_k   for every active shift, and
+// p_0 = r + beta p_0 for the base system (its x is updated with r); r read once
 template <int F>
 __global__ __launch_bounds__(256) void k_ms_update(Spinor<F> x, Spinor<F> p, Spinor<F> r,
                                                    const CgState *__restrict__ base_, const MsState *ms_,
@@ -99,6 +125,18 @@ __global__ __launch_bounds__(256) void k_ms_update(Spinor<F> x, Spinor<F> p, Spi
     typedef typename RealOf<F>::T R;
     cx<R> rv[3];
     r.rhs(j).load(h, rv);
+    {
+        const R b = (R)base_[j].beta;
+        const Spinor<F> P = p.rhs(j);
+        cx<R> pv[3];
+        P.load(h, pv);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            pv[c].re = rv[c].re + b * pv[c].re;
+            pv[c].im = rv[c].im + b * pv[c].im;
+        }
+        P.store(h, pv);
+    }
     for (int k = 1; k < nshift; ++k) {
         const MsState &S = ms[k];
         if (!S.active) continue;
@@ -168,6 +206,20 @@ __global__ __launch_bounds__(256) void k_replicate(Spinor<F64> src, Spinor<F> ds
 struct MsWorkspace {
     DevBuf t, q, r, p0, pk, part, state, ms, gl, diag, bstack;
 };
+
+// What follows the two Dslash launches of an iteration (partials of <p, q> of
+// every source in `part`, nba each), in four launches.  With one per scalar step
+// (eight, several of one block) the iteration took 54 us on 24^3 x 8 with two
+// sources and 12 shifts, of which the Dslash 25.
+template <int K>
+static void ms_iteration_tail(int vh, int m, int ns, int nba, Spinor<K> X, Spinor<K> P, Spinor<K> R, const void *q,
+                              CgState *base, MsState *ms, MsGlobal *gl, double *part, hipStream_t s) {
+    launch_reduce(RED_ALPHA, m, part, nba, base, nullptr, s);
+    launch_update_xr(K, vh, m, X.p, R.p, P.p, q, base, part, s);
+    hipLaunchKernelGGL(k_ms_scalars, dim3(m), dim3(256), 0, s, part, blas_blocks(vh), base, ms, gl, ns);
+    hipLaunchKernelGGL(k_ms_update<K>, dim3((vh + 255) / 256, m), dim3(256), 0, s, X, P, R, base, ms, ns, m,
+                       (int)CG_RUNNING);
+}
 
 // Multi-shift CG for nsrc sources in lockstep, its Krylov iteration in
 // precision K (FP32: the mixed form; FP64).  Links and vectors of the
@@ -274,15 +326,7 @@ static int multishift_solve_lockstep(hisq_gauge_s *g, double mass, int m, int ns
         if ((r2 = gauge_dslash(g, 1, K, K, K, m, p0, tk.p, nullptr, nullptr, nullptr, base, st))) return r2;
         if ((r2 = gauge_dslash(g, 0, K, K, K, m, tk.p, qk.p, p0, (const double *)diag.p, pt, base, st)))
             return r2;
-        launch_reduce(RED_ALPHA, m, pt, nb_dslash(g, K, K, K, m, true), base, nullptr, st);
-        hipLaunchKernelGGL(k_ms_alpha, shift_grid, dim3(tb), 0, st, base, ms, gl, ns);
-        launch_update_xr(K, vh, m, xk.p, rk.p, p0, qk.p, base, pt, st);
-        launch_reduce(RED_BETA, m, pt, nb, base, nullptr, st);
-        hipLaunchKernelGGL(k_ms_beta, beta_grid, beta_block, 0, st, base, ms, gl, ns, (int)CG_RUNNING);
-        hipLaunchKernelGGL(k_ms_update<K>, site_grid, dim3(256), 0, st, X, P, Rv, base, ms, ns, m,
-                           (int)CG_RUNNING);
-        hipLaunchKernelGGL(k_ms_clear_pending, shift_grid, dim3(tb), 0, st, base, ms, ns, (int)CG_RUNNING);
-        launch_update_p(K, vh, m, rk.p, p0, base, CG_RUNNING, st);
+        ms_iteration_tail<K>(vh, m, ns, nb_dslash(g, K, K, K, m, true), X, P, Rv, qk.p, base, ms, gl, pt, st);
         return (int)(hipGetLastError() == hipSuccess ? HISQ_OK : HISQ_ERR_HIP);
     };
     // FP64 reliable update of the base systems flagged CG_ATTENTION
@@ -300,7 +344,6 @@ static int multishift_solve_lockstep(hisq_gauge_s *g, double mass, int m, int ns
         hipLaunchKernelGGL(k_ms_update<K>, site_grid, dim3(256), 0, s, X, P, Rv, base, ms, ns, m,
                            (int)CG_RESUME);
         hipLaunchKernelGGL(k_ms_clear_pending, shift_grid, dim3(tb), 0, s, base, ms, ns, (int)CG_RESUME);
-        launch_update_p(K, vh, m, rk.p, p0, base, CG_RESUME, s);
         launch_resume_flags(m, base, s);
         return (int)(hipGetLastError() == hipSuccess ? HISQ_OK : HISQ_ERR_HIP);
     };
@@ -491,17 +534,7 @@ int multishift_solve(hisq_gauge_s *g, double mass, int ns, const double *shifts,
         if ((r2 = gauge_dslash(g, 0, F64, F64, F64, 1, w.t.p, w.q.p, p0, (const double *)w.diag.p,
                                (double *)w.part.p, base, st)))
             return r2;
-        launch_reduce(RED_ALPHA, 1, (double *)w.part.p, nb_d0, base, nullptr, st);
-        const int tb = 64, gb = (ns + tb - 1) / tb;
-        hipLaunchKernelGGL(k_ms_alpha, dim3(gb), dim3(tb), 0, st, base, ms, gl, ns);
-        launch_update_xr(F64, vh, 1, xs.p, w.r.p, p0, w.q.p, base, (double *)w.part.p, st);
-        launch_reduce(RED_BETA, 1, (double *)w.part.p, nb, base, nullptr, st);
-        hipLaunchKernelGGL(k_ms_beta, dim3(1), dim3(std::max(64, ((ns + 63) / 64) * 64)), 0, st, base, ms,
-                           gl, ns, (int)CG_RUNNING);
-        hipLaunchKernelGGL(k_ms_update<F64>, dim3((vh + 255) / 256), dim3(256), 0, st, X, P, Rv, base, ms, ns, 1,
-                           (int)CG_RUNNING);
-        hipLaunchKernelGGL(k_ms_clear_pending, dim3(gb), dim3(tb), 0, st, base, ms, ns, (int)CG_RUNNING);
-        launch_update_p(F64, vh, 1, w.r.p, p0, base, CG_RUNNING, st);
+        ms_iteration_tail<F64>(vh, 1, ns, nb_d0, X, P, Rv, w.q.p, base, ms, gl, (double *)w.part.p, st);
         return (int)(hipGetLastError() == hipSuccess ? HISQ_OK : HISQ_ERR_HIP);
     };
 
