@@ -26,20 +26,10 @@ __device__ __forceinline__ double block_sum(double v) {
     return s;
 }
 
-// Sum of nb partials over the block in a fixed order; valid in thread 0.  Eight
-// loads are in flight per thread (one after another, a round trip each, cost
-// 1.4 us of 4.0 at nb = 1024).
+// Sum of nb partials over the block in a fixed order; valid in thread 0.
 __device__ __forceinline__ double reduce_partials(const double *part, int nb) {
-    constexpr int U = 8;
-    const int step = blockDim.x;
     double s = 0.0;
-    for (int i = threadIdx.x; i < nb; i += U * step) {
-        double v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = i + u * step < nb ? part[i + u * step] : 0.0;
-#pragma unroll
-        for (int u = 0; u < U; ++u) s = i + u * step < nb ? s + v[u] : s;
-    }
+    for (int i = threadIdx.x; i < nb; i += blockDim.x) s += part[i];
     return block_sum(s);
 }
 
