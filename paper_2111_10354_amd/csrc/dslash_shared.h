@@ -7,13 +7,14 @@
 // units into registers while the current stage is applied, and stores them to
 // the other LDS buffer at its end, so a link byte crosses the caches once for
 // all right-hand sides and no thread keeps a slot's link for longer than its
-// product.  The gathers of slot k + 1 are issued before the product of slot k.
+// product.  The gathers of the next slots (gather_depth) are issued before the
+// product of slot k.
 //
 // What bounds it (48^3 x 12, FP32, 16 right-hand sides: 1.15 GB, 0.157 ms at
 // the 7.3 TB/s that cross the L2s; 12.2 GFLOP on the vector ALUs, 0.155 ms):
 // both, and how well they overlap.  A thread with 4 RHS in its RHS tile and the
 // compiler's schedule holds 185 registers (two wavefronts per SIMD) and took
-// 0.436 ms in the best shape, 0.62 ms in the default one; here R = 4 takes 136
+// 0.436 ms in the best shape, 0.62 ms in the default one; here R = 4 takes 158
 // (three wavefronts) and 0.338 ms, in FP64 0.796 ms instead of 1.78 ms.
 // The tiles are swept in columns (link_tile_order): 0.45 ms in memory order.
 #pragma once
@@ -43,28 +44,41 @@ struct Stage {
     }
 };
 
+// Colour vector as it lies in memory.  It is unpacked where it is used: an
+// unpacking (FP16S) next to the load would wait for it there.
+template <int F> struct Packed { u4v a; };
+template <> struct Packed<F32> { f4v a; f2v b; };
+template <> struct Packed<F64> { d2v a[3]; };
+
 // Colour vector of site nb from a field whose base is the same for the whole
 // wavefront: 32-bit byte offsets (Vh < 2^28), so one offset register serves
 // every right-hand side and the bases stay in scalar registers.
 template <int F>
-__device__ __forceinline__ void load_vector(const char *base, int vh, unsigned nb, cx<typename RealOf<F>::T> v[3]) {
+__device__ __forceinline__ void load_packed(const char *base, int vh, unsigned nb, Packed<F> &v) {
     if constexpr (F == F64) {
         const size_t plane = (size_t)vh * 16;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const d2v a = *(const d2v *)(base + c * plane + nb * 16u);
-            v[c] = {a.x, a.y};
-        }
+        for (int c = 0; c < 3; ++c) v.a[c] = *(const d2v *)(base + c * plane + nb * 16u);
     } else if constexpr (F == F32) {
-        const f4v a = *(const f4v *)(base + nb * 16u);
-        const f2v b = *(const f2v *)(base + (size_t)vh * 16 + nb * 8u);
-        v[0] = {a.x, a.y};
-        v[1] = {a.z, a.w};
-        v[2] = {b.x, b.y};
+        v.a = *(const f4v *)(base + nb * 16u);
+        v.b = *(const f2v *)(base + (size_t)vh * 16 + nb * 8u);
     } else {
-        const u4v rec = *(const u4v *)(base + nb * 16u);
-        const h8v a = __builtin_bit_cast(h8v, rec);
-        const unsigned int sw = rec.w;
+        v.a = *(const u4v *)(base + nb * 16u);
+    }
+}
+
+template <int F>
+__device__ __forceinline__ void unpack(const Packed<F> &p, cx<typename RealOf<F>::T> v[3]) {
+    if constexpr (F == F64) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v[c] = {p.a[c].x, p.a[c].y};
+    } else if constexpr (F == F32) {
+        v[0] = {p.a.x, p.a.y};
+        v[1] = {p.a.z, p.a.w};
+        v[2] = {p.b.x, p.b.y};
+    } else {
+        const h8v a = __builtin_bit_cast(h8v, p.a);
+        const unsigned int sw = p.a.w;
         const float sc = __builtin_bit_cast(float, sw);
 #pragma unroll
         for (int c = 0; c < 3; ++c) v[c] = {(float)a[2 * c] * sc, (float)a[2 * c + 1] * sc};
@@ -138,6 +152,14 @@ __device__ __forceinline__ void settle(cx<T> v[3]) {
     asm volatile("" : "+v"(v[0].re), "+v"(v[0].im), "+v"(v[1].re), "+v"(v[1].im), "+v"(v[2].re), "+v"(v[2].im)::"memory");
 }
 
+// Slots whose gathers are in flight ahead of the product, for R right-hand
+// sides of format SI per thread.  One slot against two: FP16S 28x22x18x10 with
+// 5 RHS 20.4 -> 18.2 us (its records are also unpacked at the product now), FP64
+// 48^3 x 12 with 8 RHS 0.448 -> 0.427 ms, FP32 there with 4 to 16 RHS the same
+// within 1 %; three slots add nothing.  Not FP64 with R = 4, which holds 243
+// registers already: 0.804 -> 0.921 ms.
+constexpr int gather_depth(int SI, int R) { return SI == F64 && R > 3 ? 1 : 2; }
+
 template <int LF, int SI, int SO, int R, int W, bool EPI, int CM, bool NT>
 __global__ __launch_bounds__(64 * W) void dslash_shared_kernel(Geom g, const void *__restrict__ lptr, Spinor<SI> in,
                                                                Spinor<SO> out, Spinor<SI> y,
@@ -147,6 +169,7 @@ __global__ __launch_bounds__(64 * W) void dslash_shared_kernel(Geom g, const voi
                                                                const int *__restrict__ tiles) {
     typedef typename RealOf<LF>::T T;
     typedef Stage<LF, CM> S;
+    constexpr int DEPTH = gather_depth(SI, R);
     constexpr int PU = (S::US + W - 1) / W;  // units a wavefront stages
     __shared__ u4v lds[2][S::US * 64];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -185,12 +208,12 @@ __global__ __launch_bounds__(64 * W) void dslash_shared_kernel(Geom g, const voi
     };
     // index of the neighbour of slot k = 4 mu + j
     auto neighbour = [&](int k) { return hop_index(g, sc, h, k >> 2, slot_dist(k & 3)); };
-    cx<T> v[2][R][3];
+    Packed<SI> v[DEPTH + 1][R];
     auto gather = [&](int b, int k) {
         const int nb = neighbour(k);
 #pragma unroll
         for (int r = 0; r < R; ++r)
-            load_vector<SI>((const char *)in.rhs(rhs_of(r)).p, g.vh, (unsigned)nb, v[b][r]);
+            load_packed<SI>((const char *)in.rhs(rhs_of(r)).p, g.vh, (unsigned)nb, v[b][r]);
     };
 
     cx<T> acc[R][3];
@@ -199,26 +222,31 @@ __global__ __launch_bounds__(64 * W) void dslash_shared_kernel(Geom g, const voi
 #pragma unroll
         for (int c = 0; c < 3; ++c) acc[r][c] = {T(0), T(0)};
 
+    // slot (4 mu + j) of the K-th of the sixteen products
+    auto slot_of = [](int K) { return K / S::SPS * S::SPS + S::rel_slot(K % S::SPS); };
     // every stage and slot unrolled: no branch, so no product moves past the
     // barriers that keep one slot's gathers in flight and not all of them
     fetch(0);
-    gather(0, S::rel_slot(0));
+    for_slots([&](auto kc) { gather(decltype(kc)::value, slot_of(decltype(kc)::value)); },
+              std::make_integer_sequence<int, DEPTH>{});
     stash(0);
     __syncthreads();
     auto slot = [&](auto kc) {
         constexpr int K = decltype(kc)::value, s = K / S::SPS, I = K % S::SPS;
         if constexpr (I == 0 && s + 1 < S::NS) fetch(s + 1);
-        if constexpr (K + 1 < 16)
-            gather((K + 1) & 1, (K + 1) / S::SPS * S::SPS + S::rel_slot((K + 1) % S::SPS));
+        if constexpr (K + DEPTH < 16) gather((K + DEPTH) % (DEPTH + 1), slot_of(K + DEPTH));
         __builtin_amdgcn_sched_barrier(0);
         cx<T> m[9];
         stage_matrix<LF, CM, I>(&lds[s & 1][lane], signs, s * S::SPS / 4, m);
 #pragma unroll
-        for (int r = 0; r < R; ++r)
+        for (int r = 0; r < R; ++r) {
+            cx<T> x[3];
+            unpack<SI>(v[K % (DEPTH + 1)][r], x);
 #pragma unroll
             for (int a = 0; a < 3; ++a)
 #pragma unroll
-                for (int b = 0; b < 3; ++b) cmac(acc[r][a], m[3 * a + b], v[K & 1][r][b]);
+                for (int b = 0; b < 3; ++b) cmac(acc[r][a], m[3 * a + b], x[b]);
+        }
 #pragma unroll
         for (int r = 0; r < R; ++r) settle(acc[r]);
         __builtin_amdgcn_sched_barrier(0);
