@@ -192,9 +192,10 @@ int hisq_dslash_eo(hisq_gauge_t g, int out_parity, int prec, const void *in, voi
  * formed from, this is (A + sigma_i) y_i.  For FP16S the epilogue output is
  * written as FP16S too.  The RHS tile and block shape come from the
  * autotuner's table (defaults if the shape was never tuned).  The stacks in
- * and out (and y and out) must not overlap.  diag is copied to a buffer of
- * the handle (grown, with a synchronisation, only for nrhs > 64); calls on
- * different streams are ordered on the device around that buffer.
+ * and out (and y and out) must not overlap.  Up to 16 coefficients travel
+ * with the launch; more are copied to a buffer of the handle (grown, with a
+ * synchronisation, only for nrhs > 64), and such calls on different streams
+ * are ordered on the device around that buffer.
  * Errors: -1 bad arguments (nrhs < 1, y without diag, overlapping stacks),
  * -4 precision not packed.
  */
@@ -204,13 +205,13 @@ int hisq_dslash_multi_rhs(hisq_gauge_t g, int out_parity, int prec, int nrhs, co
 /*
  * hisq_dslash_multi_rhs for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc): same arguments, semantics and output.  The per-RHS epilogue
- * coefficients are staged in a fixed device array of HISQ_NOALLOC_MAX_RHS
- * doubles per GPU, set up by hisq_gauge_create and kept until the process
- * ends, so the call allocates nothing.  Every call on one GPU shares that
- * array: calls with diag that overlap in time on one GPU (different streams
- * or threads without ordering) race on it; calls ordered on one stream do
- * not.  diag is read during the call (host), y/in/out as for
+ * hipMalloc): same arguments, semantics and output.  Per-RHS epilogue
+ * coefficients of more than 16 right-hand sides are staged in a fixed device
+ * array of HISQ_NOALLOC_MAX_RHS doubles per GPU, set up by hisq_gauge_create
+ * and kept until the process ends, so the call allocates nothing.  Every such
+ * call on one GPU shares that array: calls with diag that overlap in time on
+ * one GPU (different streams or threads without ordering) race on it; calls
+ * ordered on one stream do not.  diag is read during the call (host), y/in/out as for
  * hisq_dslash_multi_rhs.
  * Errors: those of hisq_dslash_multi_rhs, and -1 if diag is given with nrhs >
  * HISQ_NOALLOC_MAX_RHS.

@@ -189,7 +189,8 @@ int tune_dslash(hisq_gauge_s *g, int fl, int fi, int fo, int nrhs, bool epi, con
         a.in = in.p;
         a.out = dst;
         a.y = epi ? y.p : nullptr;
-        a.diag = epi ? (const double *)diag.p : nullptr;
+        a.epilogue = epi;
+        a.diag.p = (const double *)diag.p;
         a.partials = epi ? (double *)part.p : nullptr;
         a.skip = nullptr;
         a.nrhs = nrhs;

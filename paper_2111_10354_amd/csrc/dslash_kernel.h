@@ -63,7 +63,7 @@ enum { MODE_PLAIN = 0, MODE_XROW = 1, MODE_TMARCH = 2 };
 template <int LF, int SI, int SO, int TILE, bool EPI, int CM, int RS, int MODE, bool NT>
 __global__ __launch_bounds__(256) void dslash_kernel(Geom g, const void *__restrict__ lptr, Spinor<SI> in,
                                                      Spinor<SO> out, Spinor<SI> y,
-                                                     const double *__restrict__ diag,
+                                                     Coefs diag,
                                                      double *__restrict__ partials,
                                                      const CgState *__restrict__ skip, int parity,
                                                      int nrhs, int order) {
@@ -419,7 +419,7 @@ static int launch_tile(const Geom &g, const DslashLaunch &a, hipStream_t s) {
 
 template <int LF, int SI, int SO>
 int launch_epi(const Geom &g, const DslashLaunch &a, hipStream_t s) {
-    return a.diag ? launch_tile<LF, SI, SO, true>(g, a, s) : launch_tile<LF, SI, SO, false>(g, a, s);
+    return a.epilogue ? launch_tile<LF, SI, SO, true>(g, a, s) : launch_tile<LF, SI, SO, false>(g, a, s);
 }
 
 }  // namespace hisq

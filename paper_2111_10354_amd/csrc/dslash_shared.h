@@ -163,7 +163,7 @@ constexpr int gather_depth(int SI, int R) { return SI == F64 && R > 3 ? 1 : 2; }
 template <int LF, int SI, int SO, int R, int W, bool EPI, int CM, bool NT>
 __global__ __launch_bounds__(64 * W) void dslash_shared_kernel(Geom g, const void *__restrict__ lptr, Spinor<SI> in,
                                                                Spinor<SO> out, Spinor<SI> y,
-                                                               const double *__restrict__ diag,
+                                                               Coefs diag,
                                                                double *__restrict__ partials,
                                                                const CgState *__restrict__ skip, int parity, int nrhs,
                                                                const int *__restrict__ tiles) {
@@ -315,7 +315,7 @@ static void launch_shared_comp(const Geom &g, const DslashLaunch &a, hipStream_t
 
 template <int LF, int SI, int SO, int R, int W>
 static int launch_shared_rw(const Geom &g, const DslashLaunch &a, hipStream_t s) {
-    if (a.diag) launch_shared_comp<LF, SI, SO, R, W, true>(g, a, s);
+    if (a.epilogue) launch_shared_comp<LF, SI, SO, R, W, true>(g, a, s);
     else launch_shared_comp<LF, SI, SO, R, W, false>(g, a, s);
     return 0;
 }

@@ -569,6 +569,15 @@ void launch_long_link_defect(const Geom &g, const double *lng, unsigned *defect_
 
 struct CgState;
 
+// Epilogue coefficients: per right-hand side in device memory (the solvers keep
+// theirs there), or, with p null, the first Coefs::N of them in the launch itself.
+struct Coefs {
+    static constexpr int N = 16;
+    const double *p;
+    double v[N];
+    __device__ __forceinline__ double operator[](int i) const { return p ? p[i] : v[i]; }
+};
+
 // Dslash with optional epilogue out = diag_i * y_i - D in_i and per-block
 // partial sums of Re<y_i, out_i> (FP64).  nrhs >= 1, tile = RHS per thread.
 struct DslashLaunch {
@@ -576,7 +585,8 @@ struct DslashLaunch {
     const void *in;
     void *out;
     const void *y;          // epilogue input (null = plain Dslash)
-    const double *diag;     // device, per RHS (null = plain Dslash)
+    bool epilogue;
+    Coefs diag;             // of the epilogue
     double *partials;       // device [nrhs][nblocks] (null = no dot)
     const CgState *skip;    // device per-RHS solver state: a tile whose RHS are all
                             // not running is skipped (null = compute all)

@@ -1,7 +1,8 @@
 // hisq_dslash_multi_rhs for callers that cannot allocate device memory.
 //
 // The only device memory the epilogue form needs beyond the caller's buffers
-// is the per-RHS coefficient array.  Here it lives in a fixed array of the
+// is the per-RHS coefficient array, where the coefficients are too many to
+// travel with the launch (Coefs::N).  Here it lives in a fixed array of the
 // library's code object, one copy per GPU, so a call allocates nothing.  Host
 // code never uses the array's name as an address (in host code it is only a
 // stand-in symbol): the address of each device's copy is looked up once, with
@@ -60,6 +61,7 @@ extern "C" int hisq_dslash_multi_rhs_noalloc(hisq_gauge_t g, int out_parity, int
         set_error("hisq_dslash_multi_rhs_noalloc: the handle's device must be current");
         return HISQ_ERR_INVALID;
     }
+    if (nrhs <= Coefs::N) return gauge_dslash_host_diag(g, out_parity, prec, nrhs, in, out, y, diag, s);
     double *coef = nullptr;
     if ((rc = scratch_for(dev, &coef))) return rc;
     // stream-ordered: the kernel below reads what this copy writes

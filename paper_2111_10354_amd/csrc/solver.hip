@@ -98,21 +98,21 @@ DslashShape pick_shape(hisq_gauge_s *g, int fl, int fi, int fo, int nrhs, bool e
 // 48^3 x 12 FP32 (1.2 GiB) 129 / 119.
 bool links_cached(const hisq_gauge_s *g, int fl) { return g->links[fl][0].bytes <= ((size_t)128 << 20); }
 
-int gauge_dslash(hisq_gauge_s *g, int out_parity, int fl, int fi, int fo, int nrhs, const void *in,
-                 void *out, const void *y, const double *diag_dev, double *partials, const CgState *skip,
-                 hipStream_t s) {
+static int dslash_on(hisq_gauge_s *g, int out_parity, int fl, int fi, int fo, int nrhs, const void *in, void *out,
+                     const void *y, const Coefs *diag, double *partials, const CgState *skip, hipStream_t s) {
     const void *links = g->links[fl][out_parity].p;
     if (!links) {
         set_error("links of this precision were not packed (prec_mask)");
         return HISQ_ERR_UNSUPPORTED;
     }
-    const DslashShape sh = pick_shape(g, fl, fi, fo, nrhs, diag_dev != nullptr);
+    const DslashShape sh = pick_shape(g, fl, fi, fo, nrhs, diag != nullptr);
     DslashLaunch a{};
     a.links = links;
     a.in = in;
     a.out = out;
     a.y = y;
-    a.diag = diag_dev;
+    a.epilogue = diag != nullptr;
+    if (diag) a.diag = *diag;
     a.partials = partials;
     a.skip = skip;
     a.nrhs = nrhs;
@@ -127,6 +127,21 @@ int gauge_dslash(hisq_gauge_s *g, int out_parity, int fl, int fi, int fo, int nr
     a.cached = links_cached(g, fl);
     a.tiles = (const int *)g->tile_order.p;
     return launch_dslash(g->geom, a, s);
+}
+
+int gauge_dslash(hisq_gauge_s *g, int out_parity, int fl, int fi, int fo, int nrhs, const void *in,
+                 void *out, const void *y, const double *diag_dev, double *partials, const CgState *skip,
+                 hipStream_t s) {
+    Coefs c{};
+    c.p = diag_dev;
+    return dslash_on(g, out_parity, fl, fi, fo, nrhs, in, out, y, diag_dev ? &c : nullptr, partials, skip, s);
+}
+
+int gauge_dslash_host_diag(hisq_gauge_s *g, int out_parity, int prec, int nrhs, const void *in, void *out,
+                           const void *y, const double *diag, hipStream_t s) {
+    Coefs c{};
+    for (int i = 0; i < nrhs; ++i) c.v[i] = diag[i];
+    return dslash_on(g, out_parity, prec, prec, prec, nrhs, in, out, y, &c, nullptr, nullptr, s);
 }
 
 // ------------------------------------------------------------------ workspace

@@ -199,6 +199,11 @@ int gauge_dslash(hisq_gauge_s *g, int out_parity, int fmt_links, int fmt_in, int
                  const void *in, void *out, const void *y, const double *diag_dev, double *partials,
                  const CgState *skip, hipStream_t s);
 
+// The same with an epilogue whose coefficients, diag[nrhs], nrhs <= Coefs::N,
+// are in host memory: they travel with the launch.
+int gauge_dslash_host_diag(hisq_gauge_s *g, int out_parity, int prec, int nrhs, const void *in, void *out,
+                           const void *y, const double *diag, hipStream_t s);
+
 int nb_dslash(hisq_gauge_s *g, int fl, int fi, int fo, int n, bool epi);
 
 // Time the candidate launch shapes (or read them from `cache`) and install the best.
