@@ -91,20 +91,23 @@ __device__ __forceinline__ void unit_entries(const u4v *u, cx<typename RealOf<LF
     if constexpr (LF == F64) {
 #pragma unroll
         for (int e = 0; e < N; ++e) {
-            const d2v a = __builtin_bit_cast(d2v, u[(E0 + e) * 64]);
+            const u4v raw = u[(E0 + e) * 64];
+            const d2v a = __builtin_bit_cast(d2v, raw);
             w[e] = {a.x, a.y};
         }
     } else if constexpr (LF == F32) {
 #pragma unroll
         for (int q = E0 / 2; q <= (E0 + N - 1) / 2; ++q) {
-            const f4v a = __builtin_bit_cast(f4v, u[q * 64]);
+            const u4v raw = u[q * 64];
+            const f4v a = __builtin_bit_cast(f4v, raw);
             if (2 * q >= E0 && 2 * q < E0 + N) w[2 * q - E0] = {a.x, a.y};
             if (2 * q + 1 >= E0 && 2 * q + 1 < E0 + N) w[2 * q + 1 - E0] = {a.z, a.w};
         }
     } else {
 #pragma unroll
         for (int q = E0 / 4; q <= (E0 + N - 1) / 4; ++q) {
-            const h8v a = __builtin_bit_cast(h8v, u[q * 64]);
+            const u4v raw = u[q * 64];
+            const h8v a = __builtin_bit_cast(h8v, raw);
 #pragma unroll
             for (int k = 0; k < 4; ++k)
                 if (4 * q + k >= E0 && 4 * q + k < E0 + N) w[4 * q + k - E0] = {(float)a[2 * k], (float)a[2 * k + 1]};
