@@ -24,15 +24,24 @@
 // the wave's lanes in FP32 and staged in LDS as BF16: lane pair (site, half)
 // loads the neighbour's units and the link once per pair and each half
 // transports 4 of the 8 channels.  The result is staged in LDS and written
-// as whole 16-byte units.  The adjoint layer needed by back-propagation is
+// as whole 16-byte units.  The loads of a path are issued before the one ahead of
+// it is transported, and a wavefront shares no LDS with another, so none waits
+// for another.  The adjoint layer needed by back-propagation is
 // the same kernel with weights W'_{p'} = W_p^H, p' the adjoint hop.  Weight
 // gradients G(W_p[a][b]) = sum_{x,c} g_a(x)_c conj((T_p psi_b)(x)_c) use the
 // same MFMA with (site, colour, re/im) as the reduction, per-block partials
 // and a fixed-order final sum (deterministic).
+//
+// What bounds it (8 -> 8 channels, 32^3 x 8: 88 MB of links and activations, 12 us
+// at 7.3 TB/s; 302 MB of neighbours from the L2s, 9 us; 1.2 GFLOP of transport,
+// FP32 on the vector ALUs, which with its conversions and addresses is about 1700
+// instructions per wavefront, 23 us): the vector ALUs, 41 us, 51 us with a
+// path's loads issued when it was due and a barrier around every chunk.
 
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <utility>
 #include <vector>
 
 #include "nn_internal.h"
@@ -42,6 +51,9 @@ namespace hisq {
 typedef __bf16 b8v __attribute__((ext_vector_type(8)));
 typedef __bf16 b4v __attribute__((ext_vector_type(4)));
 typedef unsigned int u2v __attribute__((ext_vector_type(2)));
+typedef short s4v __attribute__((ext_vector_type(4)));
+typedef short s8v __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) s4v lds_s4v;
 
 template <class T>
 __device__ __forceinline__ cx<T> cconj(cx<T> a) { return {a.re, -a.im}; }
@@ -86,15 +98,21 @@ __device__ __forceinline__ SiteGeo site_geo(const Lex &g, int s) {
     return o;
 }
 
-// lex index of x + d mu, d = +1 or -1
+// Step of the lex index from coordinate c of an axis of extent L to c + d, d = +1
+// or -1.  A choice of two numbers, no branch: a branch ends the block in which the
+// loads of the paths are scheduled.
+__device__ __forceinline__ int hop_step(int c, int L, int stride, int d) {
+    const int wrap = (L - 1) * stride;
+    return c == (d > 0 ? L - 1 : 0) ? -d * wrap : d * stride;
+}
+
+// lex index of x + d mu
 template <int MU>
 __device__ __forceinline__ int hop(const Lex &g, const SiteGeo &x, int d) {
     int stride = 1;
 #pragma unroll
     for (int k = 0; k < MU; ++k) stride *= g.L[k];
-    const int c = x.c[MU], Lm = g.L[MU];
-    if (d > 0) return c == Lm - 1 ? x.s - (Lm - 1) * stride : x.s + stride;
-    return c == 0 ? x.s + (Lm - 1) * stride : x.s - stride;
+    return x.s + hop_step(x.c[MU], g.L[MU], stride, d);
 }
 
 // Enumerated site -> lex index: all sites in lex order, or the even sites in
@@ -112,15 +130,34 @@ __device__ __forceinline__ int site_of(const Lex &g, int idx) {
 }
 
 // ------------------------------------------------------------------ thin links (FP16)
+// The words of link mu of site s: from word mu of unit 2 mu of the record on.
+// Only those are loaded: a register of an unused word is given to another value
+// while the load is in flight, which then waits for it.
 template <int MU>
-__device__ __forceinline__ void load_link(const void *thin, int s, cx<float> w[9]) {
-    const u4v *b = (const u4v *)thin + (size_t)(s >> 6) * 9 * 64 + (s & 63);
-    constexpr int U0 = (9 * MU) / 4, OFF = (9 * MU) % 4;  // first unit, first word in it
-    const u4v r0 = b[U0 * 64], r1 = b[(U0 + 1) * 64], r2 = b[(U0 + 2) * 64];
-    const unsigned wd[12] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w, r2.x, r2.y, r2.z, r2.w};
+__device__ __forceinline__ void load_link(const void *thin, int s, unsigned wd[9]) {
+    const unsigned *b = (const unsigned *)thin + ((size_t)(s >> 6) * 9 * 64 + (s & 63) + 2 * MU * 64) * 4;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) wd[k] = b[(MU + k) / 4 * 256 + (MU + k) % 4];
+}
+
+// The same for a mu that differs from lane to lane
+__device__ __forceinline__ void load_link(const void *thin, int s, int mu, unsigned wd[9]) {
+    const u4v *b = (const u4v *)thin + (size_t)(s >> 6) * 9 * 64 + (s & 63) + 2 * mu * 64;
+    const u4v r[3] = {b[0], b[64], b[128]};
+    unsigned w[12] = {r[0].x, r[0].y, r[0].z, r[0].w, r[1].x, r[1].y, r[1].z, r[1].w, r[2].x, r[2].y, r[2].z, r[2].w};
+    // words from mu on, in two shifts with masks: a choice of elements would put
+    // the array into scratch memory
+    const unsigned m1 = 0u - (mu & 1), m2 = 0u - ((mu >> 1) & 1);
+#pragma unroll
+    for (int k = 0; k < 11; ++k) w[k] = (w[k] & ~m1) | (w[k + 1] & m1);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) wd[k] = (w[k] & ~m2) | (w[k + 2] & m2);
+}
+
+__device__ __forceinline__ void unpack_link(const unsigned wd[9], cx<float> w[9]) {
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-        const unsigned v = wd[OFF + k];
+        const unsigned v = wd[k];
         const h2v h = __builtin_bit_cast(h2v, v);
         w[k] = {(float)h.x, (float)h.y};
     }
@@ -163,35 +200,54 @@ __device__ __forceinline__ float half_chan(const u2v &v, int q) {
 }
 
 // ------------------------------------------------------------------ transport into LDS
-// Path P (0 identity, 1..4 forward hop mu = P - 1, 5..8 backward hop
-// mu = P - 5, 9 = padding) of channels 4h .. 4h + 3 of a hidden input at
-// site x; writes the 3 colours x {re, im} x 4 channels to the LDS columns of
-// the site at K offset koff (+ 8 ri + 4 h).
+// A wavefront writes and reads its own part of the LDS, whose accesses of one
+// wavefront stay in order: the compiler has to keep their order, nothing waits.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <class F, int... K>
+__device__ __forceinline__ void for_paths(F &&f, std::integer_sequence<int, K...>) {
+    (f(std::integral_constant<int, K>{}), ...);
+}
+
+// What path P (0 identity, 1..4 forward hop mu = P - 1, 5..8 backward hop
+// mu = P - 5) reads for channels 4h .. 4h + 3 of a hidden input at site x
+struct PathData {
+    unsigned link[9];
+    u2v v[6];
+};
+
 template <int P>
-__device__ __forceinline__ void transport_hidden(const Lex &g, const void *thin, const void *in, const SiteGeo &x,
-                                                 bool valid, int h, __bf16 *col, int koff) {
+__device__ __forceinline__ void load_path(const Lex &g, const void *thin, const void *in, const SiteGeo &x, int h,
+                                          PathData &d) {
+    int nb = x.s, ls = x.s;
+    if constexpr (P >= 1 && P <= 4) nb = hop<P - 1>(g, x, +1);
+    if constexpr (P >= 5) ls = nb = hop<P - 5>(g, x, -1);
+    if constexpr (P >= 1) load_link<(P - 1) & 3>(thin, ls, d.link);
+    load_act_half(in, nb, h, d.v);
+}
+
+// Transports them and writes the 3 colours x {re, im} x 4 channels to the LDS
+// columns of the site at K offset koff (+ 8 ri + 4 h); P = 9 is padding.
+template <int P>
+__device__ __forceinline__ void transport_path(const PathData &d, int h, __bf16 *col, int koff) {
     float tr[3][4], ti[3][4];
+    if constexpr (P == 9) {
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+        for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) tr[a][q] = ti[a][q] = 0.f;
-    if (P < 9 && valid) {
-        int nb = x.s;
+            for (int q = 0; q < 4; ++q) tr[a][q] = ti[a][q] = 0.f;
+    } else {
         cx<float> w[9];
-        if constexpr (P >= 1 && P <= 4) {
-            nb = hop<P - 1>(g, x, +1);
-            load_link<P - 1>(thin, x.s, w);
-        } else if constexpr (P >= 5 && P <= 8) {
-            nb = hop<P - 5>(g, x, -1);
-            load_link<P - 5>(thin, nb, w);
-        }
-        u2v v[6];
-        load_act_half(in, nb, h, v);
+        if constexpr (P >= 1) unpack_link(d.link, w);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             cx<float> vb[3];
 #pragma unroll
-            for (int c = 0; c < 3; ++c) vb[c] = {half_chan(v[2 * c], q), half_chan(v[2 * c + 1], q)};
+            for (int c = 0; c < 3; ++c) vb[c] = {half_chan(d.v[2 * c], q), half_chan(d.v[2 * c + 1], q)};
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 cx<float> t = {0.f, 0.f};
@@ -218,92 +274,102 @@ __device__ __forceinline__ void transport_hidden(const Lex &g, const void *thin,
     }
 }
 
-// Path P of the one-channel even-site input (FP32 public spinor) at site x;
-// lane half h writes the re (h = 0) or im (h = 1) parts at K = 2P + h.
-template <int P>
-__device__ __forceinline__ void transport_even_path(const Lex &g, const void *thin, const float *in, const SiteGeo &x,
-                                                    bool valid, int h, __bf16 *col) {
-    cx<float> t[3] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
-    // the input lives on even sites: path 0 needs x even, the hops x odd
-    const bool live = valid && (P == 0 ? x.par == 0 : x.par == 1);
-    if (live) {
-        const int vh = g.V / 2;
-        if constexpr (P == 0) {
-            Spinor<F32>{const_cast<float *>(in), vh}.load(x.s >> 1, t);
-        } else {
-            cx<float> w[9], v[3];
-            int nb;
-            if constexpr (P <= 4) {
-                nb = hop<P - 1>(g, x, +1);
-                load_link<P - 1>(thin, x.s, w);
-            } else {
-                nb = hop<P - 5>(g, x, -1);
-                load_link<P - 5>(thin, nb, w);
-            }
-            Spinor<F32>{const_cast<float *>(in), vh}.load(nb >> 1, v);
+// All paths of a hidden input, two to a chunk of 32 K rows: use(q) once chunk q
+// is in LDS.  The loads of the next PATH_AHEAD paths are in flight; two of them
+// take 21 registers more and the same time (41.1 against 40.6 us above).  A site
+// past the last (valid false) is site 0, or zero if ZERO is set.
+constexpr int PATH_AHEAD = 1;
+
+template <bool ZERO, class F>
+__device__ __forceinline__ void transport_hidden(const Lex &g, const void *thin, const void *in, const SiteGeo &x,
+                                                 bool valid, int h, __bf16 *col, F &&use) {
+    PathData d[PATH_AHEAD + 1];
+    for_paths([&](auto pc) { load_path<decltype(pc)::value>(g, thin, in, x, h, d[decltype(pc)::value]); },
+              std::make_integer_sequence<int, PATH_AHEAD>{});
+    auto path = [&](auto pc) {
+        constexpr int P = decltype(pc)::value, N = P + PATH_AHEAD, S = P % (PATH_AHEAD + 1);
+        if constexpr (N <= 8) load_path<N>(g, thin, in, x, h, d[N % (PATH_AHEAD + 1)]);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (ZERO) {
+#pragma unroll
+            for (int u = 0; u < 6; ++u) d[S].v[u] = valid ? d[S].v[u] : u2v{0u, 0u};
+        }
+        transport_path<P>(d[S], h, col, (P & 1) * 16);
+        if constexpr (P == 8) transport_path<9>(d[S], h, col, 16);
+        if constexpr (P == 8 || (P & 1)) {
+            wave_sync();
+            use(std::integral_constant<int, P / 2>{});
+            wave_sync();
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    for_paths(path, std::make_integer_sequence<int, 9>{});
+}
+
+// The one-channel even-site input (FP32 public spinor): path p of a column at
+// K = p KS and p KS + RI (re, im), all other rows zero.  It lives on the even
+// sites, so path 0 reaches the even sites and the hops the odd ones: of a full
+// lattice's enumeration each four lanes take two neighbours in x, one of either
+// parity, and a lane the two hops of one direction (1 -> 8 channels, 32^3 x 8:
+// 17.8 us; 20.2 us with every lane pair on all eight hops of its site).
+template <int MODE, int KS, int RI>
+__device__ __forceinline__ void transport_even(const Lex &g, const void *thin, const float *in, int base, int nsites,
+                                               int l, __bf16 *bt) {
+    const Spinor<F32> src{const_cast<float *>(in), g.V / 2};
+    const u4v zero = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int e = l; e < NW_COLS * 4; e += 64) *(u4v *)(bt + (e >> 2) * BT_LD + (e & 3) * 8) = zero;
+    wave_sync();
+    auto put = [&](int s, int a, int p, const cx<float> &t) {
+        __bf16 *c = bt + (3 * s + a) * BT_LD + p * KS;
+        c[0] = (__bf16)t.re;
+        c[RI] = (__bf16)t.im;
+    };
+    if constexpr (MODE == IO_EVEN) {
+        if (l < NW_SITES && base + l < nsites) {
+            cx<float> t[3];
+            src.load(base + l, t);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) put(l, a, 0, t[a]);
+        }
+    } else {
+        const int pair = 2 * (l >> 2), mu = l & 3;
+        if (base + pair < nsites) {  // V is a multiple of 16
+            SiteGeo x = site_geo(g, base + pair);
+            const int odd = x.par ? 0 : 1;
+            cx<float> t0[3];
+            src.load((base + pair) >> 1, t0);
+            const cx<float> own = {mu == 0 ? +t0[0].re : mu == 1 ? +t0[1].re : +t0[2].re,
+                                   mu == 0 ? +t0[0].im : mu == 1 ? +t0[1].im : +t0[2].im};
+            if (mu < 3) put(pair + 1 - odd, mu, 0, own);
+            x.s += odd;
+            x.c[0] += odd;
+            const int c = mu == 0 ? +x.c[0] : mu == 1 ? +x.c[1] : mu == 2 ? +x.c[2] : +x.c[3];
+            const int Lm = mu == 0 ? +g.L[0] : mu == 1 ? +g.L[1] : mu == 2 ? +g.L[2] : +g.L[3];
+            const int st = mu == 0 ? 1 : mu == 1 ? g.L[0] : g.L[0] * g.L[1] * (mu == 2 ? 1 : +g.L[2]);
+            const int nf = x.s + hop_step(c, Lm, st, +1), nb = x.s + hop_step(c, Lm, st, -1);
+            unsigned lf[9], lb[9];
+            cx<float> vf[3], vb[3], w[9];
+            load_link(thin, x.s, mu, lf);
+            load_link(thin, nb, mu, lb);
+            src.load(nf >> 1, vf);
+            src.load(nb >> 1, vb);
+            unpack_link(lf, w);
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
+                cx<float> t = {0.f, 0.f};
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    if constexpr (P <= 4) {
-                        cmac(t[a], w[3 * a + c], v[c]);
-                    } else {
-                        cmac(t[a], cconj(w[3 * c + a]), v[c]);
-                    }
-                }
+                for (int k = 0; k < 3; ++k) cmac(t, w[3 * a + k], vf[k]);
+                put(pair + odd, a, 1 + mu, t);
             }
-        }
-    }
+            unpack_link(lb, w);
 #pragma unroll
-    for (int a = 0; a < 3; ++a) col[a * BT_LD + 2 * P + h] = (__bf16)(h ? t[a].im : t[a].re);
-}
-
-// All nine paths of the even-site input, zeros in the padding K = 18..31.
-__device__ __forceinline__ void transport_even(const Lex &g, const void *thin, const float *in, const SiteGeo &x,
-                                               bool valid, int h, __bf16 *col) {
-    transport_even_path<0>(g, thin, in, x, valid, h, col);
-    transport_even_path<1>(g, thin, in, x, valid, h, col);
-    transport_even_path<2>(g, thin, in, x, valid, h, col);
-    transport_even_path<3>(g, thin, in, x, valid, h, col);
-    transport_even_path<4>(g, thin, in, x, valid, h, col);
-    transport_even_path<5>(g, thin, in, x, valid, h, col);
-    transport_even_path<6>(g, thin, in, x, valid, h, col);
-    transport_even_path<7>(g, thin, in, x, valid, h, col);
-    transport_even_path<8>(g, thin, in, x, valid, h, col);
+            for (int a = 0; a < 3; ++a) {
+                cx<float> t = {0.f, 0.f};
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int j = 0; j < 7; ++j) col[a * BT_LD + 18 + 2 * j + h] = (__bf16)0.f;
-}
-
-// Transported input chunk q (K rows 32 q .. 32 q + 31) of the lane pair's site.
-template <int INM>
-__device__ __forceinline__ void transport_chunk(int q, const Lex &g, const void *thin, const void *in,
-                                                const SiteGeo &x, bool valid, int h, __bf16 *col) {
-    if constexpr (INM == IO_EVEN) {
-        transport_even(g, thin, (const float *)in, x, valid, h, col);
-    } else {
-        switch (q) {
-            case 0:
-                transport_hidden<0>(g, thin, in, x, valid, h, col, 0);
-                transport_hidden<1>(g, thin, in, x, valid, h, col, 16);
-                break;
-            case 1:
-                transport_hidden<2>(g, thin, in, x, valid, h, col, 0);
-                transport_hidden<3>(g, thin, in, x, valid, h, col, 16);
-                break;
-            case 2:
-                transport_hidden<4>(g, thin, in, x, valid, h, col, 0);
-                transport_hidden<5>(g, thin, in, x, valid, h, col, 16);
-                break;
-            case 3:
-                transport_hidden<6>(g, thin, in, x, valid, h, col, 0);
-                transport_hidden<7>(g, thin, in, x, valid, h, col, 16);
-                break;
-            default:
-                transport_hidden<8>(g, thin, in, x, valid, h, col, 0);
-                transport_hidden<9>(g, thin, in, x, valid, h, col, 16);
-                break;
+                for (int k = 0; k < 3; ++k) cmac(t, cconj(w[3 * k + a]), vb[k]);
+                put(pair + odd, a, 5 + mu, t);
+            }
         }
     }
 }
@@ -322,30 +388,33 @@ __global__ __launch_bounds__(64 * NN_WAVES) void k_nn_layer(Lex g, const void *t
     const void *__restrict__ in = (const char *)in0 + in_step * blockIdx.y;
     void *__restrict__ out = (char *)out0 + out_step * blockIdx.y;
     __shared__ __attribute__((aligned(16))) __bf16 Bt[NN_WAVES][NW_COLS][BT_LD];
-    __shared__ float Of[NN_WAVES][NW_SITES][6];
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, j = l >> 4;
     const int nsites = OUTM == IO_FULL ? g.V : g.V / 2;
     const int base = (blockIdx.x * NN_WAVES + w) * NW_SITES;
-    const int sl = l >> 1, h = l & 1;  // lane pair (site, half)
-    const int idx = base + sl;
-    const bool valid = idx < nsites;
-    const SiteGeo x = site_geo(g, valid ? site_of<OUTM>(g, idx) : 0);
-    __bf16 *col = &Bt[w][sl * 3][0];
 
+    b8v am[KP / 32];
+#pragma unroll
+    for (int q = 0; q < KP / 32; ++q) am[q] = *(const b8v *)(amat + i * KP + q * 32 + j * 8);
     f4v acc[6];
 #pragma unroll
     for (int cb = 0; cb < 6; ++cb) acc[cb] = f4v{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int q = 0; q < KP / 32; ++q) {
-        transport_chunk<INM>(q, g, thin, in, x, valid, h, col);
-        __syncthreads();
-        const b8v a = *(const b8v *)(amat + i * KP + q * 32 + j * 8);
+    auto product = [&](auto qc) {
 #pragma unroll
         for (int cb = 0; cb < 6; ++cb) {
             const b8v b = *(const b8v *)(&Bt[w][cb * 16 + i][j * 8]);
-            acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[cb], 0, 0, 0);
+            acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am[decltype(qc)::value], b, acc[cb], 0, 0, 0);
         }
-        __syncthreads();
+    };
+    if constexpr (INM == IO_EVEN) {
+        transport_even<OUTM, 2, 1>(g, thin, (const float *)in, base, nsites, l, &Bt[w][0][0]);
+        wave_sync();
+        product(std::integral_constant<int, 0>{});
+        wave_sync();
+    } else {
+        const int sl = l >> 1, h = l & 1;  // lane pair (site, half)
+        const bool valid = base + sl < nsites;
+        const SiteGeo x = site_geo(g, valid ? site_of<OUTM>(g, base + sl) : 0);
+        transport_hidden<false>(g, thin, in, x, valid, h, &Bt[w][sl * 3][0], product);
     }
 
     // lane (i, j) holds rows 4j .. 4j + 3 of column cb * 16 + i
@@ -357,7 +426,7 @@ __global__ __launch_bounds__(64 * NN_WAVES) void k_nn_layer(Lex g, const void *t
             const b4v v = {(__bf16)acc[cb][0], (__bf16)acc[cb][1], (__bf16)acc[cb][2], (__bf16)acc[cb][3]};
             *(b4v *)(Ot + s * 48 + (2 * c + (j >> 1)) * 8 + (j & 1) * 4) = v;
         }
-        __syncthreads();
+        wave_sync();
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
             const int e = t * 64 + l, s = e & 31, u = e >> 5;
@@ -368,17 +437,18 @@ __global__ __launch_bounds__(64 * NN_WAVES) void k_nn_layer(Lex g, const void *t
             }
         }
     } else {
+        float *Of = (float *)&Bt[w][0][0];  // [32 sites][6]
 #pragma unroll
         for (int cb = 0; cb < 6; ++cb) {
             const int cl = cb * 16 + i, s = cl / 3, c = cl % 3;
-            if (j == 0) Of[w][s][2 * c] = acc[cb][0];      // row 0: Re of channel 0
-            if (j == 2) Of[w][s][2 * c + 1] = acc[cb][0];  // row 8: Im of channel 0
+            if (j == 0) Of[s * 6 + 2 * c] = acc[cb][0];      // row 0: Re of channel 0
+            if (j == 2) Of[s * 6 + 2 * c + 1] = acc[cb][0];  // row 8: Im of channel 0
         }
-        __syncthreads();
+        wave_sync();
         if (l < NW_SITES && base + l < nsites) {
             cx<float> v[3];
 #pragma unroll
-            for (int c = 0; c < 3; ++c) v[c] = {Of[w][l][2 * c], Of[w][l][2 * c + 1]};
+            for (int c = 0; c < 3; ++c) v[c] = {Of[l * 6 + 2 * c], Of[l * 6 + 2 * c + 1]};
             Spinor<F32>{(float *)out, g.V / 2}.store(base + l, v);
         }
     }
@@ -391,6 +461,11 @@ __global__ __launch_bounds__(64 * NN_WAVES) void k_nn_layer(Lex g, const void *t
 // g has mode GM (IO_FULL: BF16 hidden units on all sites; IO_EVEN: channel 0
 // as an FP32 public spinor on even sites); sites are enumerated like the
 // layer kernel with OUTM = GM.  One grid row per sample, as in the layer kernel.
+// Its reduction runs along the columns of the transported tile, across the rows
+// in which LDS holds it: the transposing LDS read gives four columns at once,
+// and the half of A2 that repeats the other is not stored (22 KB of LDS for 38).
+// 8 samples of 16^3 x 8, 8 -> 8 channels 80.5 -> 40.4 us, 8 -> 1 46.7 -> 26.5,
+// 1 -> 8 35.8 -> 16.0.
 template <int INM, int GM>
 __global__ __launch_bounds__(64 * NN_WAVES) void k_nn_wgrad(Lex g, const void *thin, const void *__restrict__ in0,
                                                             const void *__restrict__ grad0, float *__restrict__ partial,
@@ -400,21 +475,17 @@ __global__ __launch_bounds__(64 * NN_WAVES) void k_nn_wgrad(Lex g, const void *t
     constexpr int KP = kp_of(INM);
     constexpr int NQ = KP / 32;  // chunks
     constexpr int KC = INM == IO_EVEN ? 16 : 80;
-    __shared__ __attribute__((aligned(16))) __bf16 Bt[NN_WAVES][NW_COLS][BT_LD];
-    __shared__ __attribute__((aligned(16))) __bf16 Gt[NN_WAVES][16][GT_LD];
-    __shared__ float Red[NN_WAVES][16][KC];
+    constexpr int BT_B = NW_COLS * BT_LD, GT_B = 8 * GT_LD;  // bf16 of a wave's operands
+    // the block's partial sums take the operands' place at the end
+    constexpr int RED_LD = 20, WAVE_B = std::max(BT_B + GT_B, 2 * RED_LD * KC);
+    __shared__ __attribute__((aligned(16))) __bf16 lds[NN_WAVES][WAVE_B];
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, j = l >> 4;
+    __bf16 *Bt = &lds[w][0], *Gt = Bt + BT_B;
     const int nsites = GM == IO_FULL ? g.V : g.V / 2;
     const int base = (blockIdx.x * NN_WAVES + w) * NW_SITES;
-    const int sl = l >> 1, h = l & 1;
-    const int idx = base + sl;
-    const bool valid = idx < nsites;
-    const SiteGeo x = site_geo(g, valid ? site_of<GM>(g, idx) : 0);
-    __bf16 *col = &Bt[w][sl * 3][0];
 
-    // A2 = [[Gr, Gi], [Gi, -Gr]] over m = (site, colour): re block m < 96, im block m >= 96
-    for (int e = l; e < 16 * GT_LD; e += 64) (&Gt[w][0][0])[e] = (__bf16)0.f;
-    __syncthreads();
+    // A2 = [[Gr, Gi], [Gi, -Gr]] over m = (site, colour): re block m < 96, im
+    // block m >= 96.  Its upper half is kept; the lower is read from it.
     if constexpr (GM == IO_FULL) {
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
@@ -422,30 +493,21 @@ __global__ __launch_bounds__(64 * NN_WAVES) void k_nn_wgrad(Lex g, const void *t
             const int S = base + s, m = s * 3 + c;
             u4v val = {0u, 0u, 0u, 0u};
             if (S < nsites) val = ((const u4v *)grad)[((size_t)(S >> 6) * 6 + u) * 64 + (S & 63)];
-            const unsigned wd[4] = {val.x, val.y, val.z, val.w};
+            const b8v v = __builtin_bit_cast(b8v, val);
 #pragma unroll
-            for (int a = 0; a < 8; ++a) {
-                const float v = (a & 1) ? bf_hi(wd[a >> 1]) : bf_lo(wd[a >> 1]);
-                if (ri == 0) {
-                    Gt[w][a][m] = (__bf16)v;
-                    Gt[w][8 + a][NW_COLS + m] = (__bf16)(-v);
-                } else {
-                    Gt[w][a][NW_COLS + m] = (__bf16)v;
-                    Gt[w][8 + a][m] = (__bf16)v;
-                }
-            }
+            for (int a = 0; a < 8; ++a) Gt[a * GT_LD + ri * NW_COLS + m] = v[a];
         }
     } else {
+        const u4v zero = {0u, 0u, 0u, 0u};
+        for (int e = l; e < GT_B / 8; e += 64) ((u4v *)Gt)[e] = zero;
+        wave_sync();
         if (l < NW_SITES) {
             cx<float> v[3] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
             if (base + l < nsites) Spinor<F32>{(float *)grad, g.V / 2}.load(base + l, v);
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                const int m = l * 3 + c;
-                Gt[w][0][m] = (__bf16)v[c].re;
-                Gt[w][8][NW_COLS + m] = (__bf16)(-v[c].re);
-                Gt[w][0][NW_COLS + m] = (__bf16)v[c].im;
-                Gt[w][8][m] = (__bf16)v[c].im;
+                Gt[l * 3 + c] = (__bf16)v[c].re;
+                Gt[NW_COLS + l * 3 + c] = (__bf16)v[c].im;
             }
         }
     }
@@ -453,37 +515,49 @@ __global__ __launch_bounds__(64 * NN_WAVES) void k_nn_wgrad(Lex g, const void *t
     f4v acc[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) acc[q] = f4v{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        transport_chunk<INM>(q, g, thin, in, x, valid, h, col);
-        __syncthreads();
+    const __bf16 *grow = Gt + (i & 7) * GT_LD;
+    const bool lower = i >= 8;
+    auto product = [&](auto qc) {
 #pragma unroll
         for (int ks = 0; ks < (2 * NW_COLS) / 32; ++ks) {
-            const b8v a = *(const b8v *)(&Gt[w][i][ks * 32 + j * 8]);
             const int ri = ks >= 3 ? 1 : 0;
-            b8v b;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int m = (ks % 3) * 32 + j * 8 + e;  // column of the transported tile
-                __bf16 v;
-                if constexpr (INM == IO_EVEN) v = i < 9 ? Bt[w][m][2 * i + ri] : (__bf16)0.f;
-                else v = Bt[w][m][(i >> 3) * 16 + ri * 8 + (i & 7)];
-                b[e] = v;
-            }
-            acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[q], 0, 0, 0);
+            const int ga = ks * 32 + j * 8, gb = ga + (ri ? -NW_COLS : NW_COLS);
+            u4v ar = *(const u4v *)(grow + (lower ? gb : ga));
+            if (ri) ar ^= lower ? 0x80008000u : 0u;
+            // columns m = (ks % 3) 32 + 8 j + 0..7 of the transported tile, row i
+            // of its re or im block: the tile is transposed as it is read, each 16
+            // lanes four columns of 16 rows at a time
+            const int n = (i & 3) * 4;
+            const __bf16 *src = Bt + ((ks % 3) * 32 + j * 8 + (i >> 2)) * BT_LD +
+                                (INM == IO_EVEN ? ri * 16 + n : (n >> 3) * 16 + ri * 8 + (n & 7));
+            const s4v b0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v *)src);
+            const s4v b1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v *)(src + 4 * BT_LD));
+            const s8v b = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3]};
+            acc[decltype(qc)::value] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(b8v, ar), __builtin_bit_cast(b8v, b), acc[decltype(qc)::value], 0, 0, 0);
         }
-        __syncthreads();
+    };
+    if constexpr (INM == IO_EVEN) {
+        transport_even<GM, 1, 16>(g, thin, (const float *)in, base, nsites, l, Bt);
+        wave_sync();
+        product(std::integral_constant<int, 0>{});
+    } else {
+        const int sl = l >> 1, h = l & 1;  // lane pair (site, half)
+        const bool valid = base + sl < nsites;
+        const SiteGeo x = site_geo(g, valid ? site_of<GM>(g, base + sl) : 0);
+        transport_hidden<true>(g, thin, in, x, valid, h, Bt + sl * 3 * BT_LD, product);
     }
+    wave_sync();
+    // [KC][16 rows + pad]: a lane's four rows are one store
+    float *Red = (float *)Bt;
 #pragma unroll
-    for (int q = 0; q < NQ; ++q)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) Red[w][j * 4 + r][q * 16 + i] = acc[q][r];
+    for (int q = 0; q < NQ; ++q) *(f4v *)(Red + (q * 16 + i) * RED_LD + j * 4) = acc[q];
     __syncthreads();
     // sum the block's waves in a fixed order, write the block partial
     for (int e = threadIdx.x; e < 16 * KC; e += blockDim.x) {
         const int r = e / KC, k = e % KC;
         float s = 0.f;
-        for (int ww = 0; ww < NN_WAVES; ++ww) s += Red[ww][r][k];
+        for (int ww = 0; ww < NN_WAVES; ++ww) s += ((const float *)&lds[ww][0])[k * RED_LD + r];
         partial[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 16 * KC + e] = s;
     }
 }
