@@ -229,8 +229,9 @@ int hisq_dslash_multi_rhs_noalloc(hisq_gauge_t g, int out_parity, int prec, int 
  * sites per thread (tiles up to 4) - and bits 24-25 log2 of the number of
  * waves a site's RHS tiles are split over; or, as order 2 without a column
  * size, W waves of RHS tiles of 1 to 4 that share the links of 64 sites
- * through LDS: block 64 W, bits 24-25 1, 2, 3 for W = 2, 4, 3) for the kernels
- * a solve in `prec`
+ * through LDS: block 64 W, bits 24-25 1, 2, 3 for W = 2, 4, 3; or order 4
+ * without a K, tile 1, block 256: the hops of 64 sites split over four waves)
+ * for the kernels a solve in `prec`
  * with `nrhs` right-hand sides launches: plain and epilogue Dslash in `prec`
  * and, if FP64 links are packed, the FP64 kernels of the reliable updates.
  * Each candidate must write bit-identical output to the default shape before

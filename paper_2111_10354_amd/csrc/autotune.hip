@@ -137,6 +137,7 @@ static int shape_rsplit(const DslashShape &s) { return 1 << ((s.order >> 24) & 3
 static bool valid_shape(const Geom &geom, int fl, int nrhs, const DslashShape &s) {
     if (const int w = shared_waves(s.order))  // a wave without a right-hand side only repeats another's work
         return shared_built(s.tile, w) && s.tile * (w - 1) < nrhs && order_supported(geom, s.order, s.block);
+    if (s.order == SPLIT_ORDER) return s.tile == 1 && order_supported(geom, s.order, s.block);
     if (s.tile < 1 || s.tile > 16 || (s.tile & (s.tile - 1)) || s.tile > std::max(1, nrhs)) return false;
     if (fl == F64 && s.tile > 4) return false;
     if ((s.order & 0xff) == 4 && s.tile > 4) return false;  // t-march: RHS tiles of up to 4
@@ -242,6 +243,14 @@ int tune_dslash(hisq_gauge_s *g, int fl, int fi, int fo, int nrhs, bool epi, con
             c.order = 3;
             if (valid_shape(G, fl, nrhs, c)) cands.push_back(c);
         }
+
+    if (nrhs * ((G.vh + 63) / 64) <= 2048) {  // the hops of few sites split over four waves
+        DslashShape c;
+        c.tile = 1;
+        c.block = 256;
+        c.order = SPLIT_ORDER;
+        if (valid_shape(G, fl, nrhs, c)) cands.push_back(c);
+    }
 
     for (int tile : {1, 2, 3, 4})  // links shared through LDS by the waves of a site tile
         for (int waves : {2, 3, 4}) {

@@ -26,7 +26,7 @@ static inline int order_rsplit(int order) { return 1 << ((order >> 24) & 3); }
 static inline int order_tiles(int order) { return order & 0xffffff; }
 
 int dslash_grid_blocks(const Geom &g, int block, int order) {
-    if (shared_waves(order)) return (g.vh + 63) / 64;
+    if (shared_waves(order) || order == SPLIT_ORDER) return (g.vh + 63) / 64;
     const int sb = block / order_rsplit(order);
     const int k = (order_tiles(order) & 0xff) == 4 ? (order >> 8) & 0xff : 1;  // t-march: K sites per thread
     const int threads = k > 0 ? g.vh / k : g.vh;
@@ -42,6 +42,7 @@ static constexpr size_t kXrowLdsMax = 64 * 1024;
 bool order_supported(const Geom &g, int order, int block) {
     if (order < 0 || (order >> 26)) return false;
     if (const int w = shared_waves(order)) return block == 64 * w && shared_supported(g);
+    if (order == SPLIT_ORDER) return block == 256 && shared_supported(g);
     const int rs = order_rsplit(order);
     if (rs == 8 || block / rs < 64) return false;  // whole waves of sites
     // x-row staging: one wave per site, workgroups of whole rows
@@ -94,7 +95,9 @@ int launch_dslash(const Geom &g, const DslashLaunch &a, hipStream_t s) {
         return HISQ_ERR_INVALID;
     }
     int rc = -1;
-    if (a.fmt_links == F64 && a.fmt_in == F64 && a.fmt_out == F64)
+    if (a.order == SPLIT_ORDER)
+        rc = a.tile == 1 ? launch_dslash_split(g, a, s) : -1;
+    else if (a.fmt_links == F64 && a.fmt_in == F64 && a.fmt_out == F64)
         rc = launch_epi<F64, F64, F64>(g, a, s);
     else if (a.fmt_links == F32 && a.fmt_in == F32 && a.fmt_out == F32)
         rc = launch_epi<F32, F32, F32>(g, a, s);

@@ -85,20 +85,20 @@ __device__ __forceinline__ void unpack(const Packed<F> &p, cx<typename RealOf<F>
     }
 }
 
-// N complex entries from entry E0 on of the 16-byte units at `u` (stride 64 units)
-template <int LF, int E0, int N>
+// N complex entries from entry E0 on of the 16-byte units at `u`, ST units apart
+template <int LF, int E0, int N, int ST = 64>
 __device__ __forceinline__ void unit_entries(const u4v *u, cx<typename RealOf<LF>::T> *w) {
     if constexpr (LF == F64) {
 #pragma unroll
         for (int e = 0; e < N; ++e) {
-            const u4v raw = u[(E0 + e) * 64];
+            const u4v raw = u[(E0 + e) * ST];
             const d2v a = __builtin_bit_cast(d2v, raw);
             w[e] = {a.x, a.y};
         }
     } else if constexpr (LF == F32) {
 #pragma unroll
         for (int q = E0 / 2; q <= (E0 + N - 1) / 2; ++q) {
-            const u4v raw = u[q * 64];
+            const u4v raw = u[q * ST];
             const f4v a = __builtin_bit_cast(f4v, raw);
             if (2 * q >= E0 && 2 * q < E0 + N) w[2 * q - E0] = {a.x, a.y};
             if (2 * q + 1 >= E0 && 2 * q + 1 < E0 + N) w[2 * q + 1 - E0] = {a.z, a.w};
@@ -106,7 +106,7 @@ __device__ __forceinline__ void unit_entries(const u4v *u, cx<typename RealOf<LF
     } else {
 #pragma unroll
         for (int q = E0 / 4; q <= (E0 + N - 1) / 4; ++q) {
-            const u4v raw = u[q * 64];
+            const u4v raw = u[q * ST];
             const h8v a = __builtin_bit_cast(h8v, raw);
 #pragma unroll
             for (int k = 0; k < 4; ++k)
@@ -115,23 +115,23 @@ __device__ __forceinline__ void unit_entries(const u4v *u, cx<typename RealOf<LF
     }
 }
 
-// The 3x3 matrix of slot I of a stage in LDS
-template <int LF, int CM, int I>
+// The 3x3 matrix of slot I of a stage, its units ST apart
+template <int LF, int CM, int I, int ST = 64>
 __device__ __forceinline__ void stage_matrix(const u4v *u, unsigned signs, int first_mu,
                                              cx<typename RealOf<LF>::T> m[9]) {
     typedef typename RealOf<LF>::T R;
     if constexpr (CM == COMP_NONE) {
-        unit_entries<LF, 9 * I, 9>(u, m);
+        unit_entries<LF, 9 * I, 9, ST>(u, m);
     } else {
         constexpr int F = 2 * CompGeom<LF>::MC, UF = CompGeom<LF>::UF, UL = CompGeom<LF>::UL;
         if constexpr (I < F) {
-            unit_entries<LF, 9 * I, 9>(u, m);
+            unit_entries<LF, 9 * I, 9, ST>(u, m);
         } else {
             constexpr int L = I - F;
-            unit_entries<LF, 6 * L, 6>(u + UF * 64, m);
+            unit_entries<LF, 6 * L, 6, ST>(u + UF * ST, m);
             if constexpr (CM == COMP_KAPPA) {
                 cx<R> kap[1];
-                unit_entries<LF, L, 1>(u + (UF + UL) * 64, kap);
+                unit_entries<LF, L, 1, ST>(u + (UF + UL) * ST, kap);
                 rebuild_row2(m, kap[0]);
             } else {
                 rebuild_row2(m, ((signs >> (2 * first_mu + L)) & 1u) ? R(-1) : R(1));

@@ -526,9 +526,13 @@ __device__ __forceinline__ void rebuild_row2(cx<R> m[9], cx<R> k) {
     const cx<R> c0 = cmul(a[1], b[2]), c1 = cmul(a[2], b[1]);
     const cx<R> c2 = cmul(a[2], b[0]), c3 = cmul(a[0], b[2]);
     const cx<R> c4 = cmul(a[0], b[1]), c5 = cmul(a[1], b[0]);
-    m[6] = cmul(k, cx<R>{c0.re - c1.re, c1.im - c0.im});
-    m[7] = cmul(k, cx<R>{c2.re - c3.re, c3.im - c2.im});
-    m[8] = cmul(k, cx<R>{c4.re - c5.re, c5.im - c4.im});
+    // the fused products named, as the compiler's choice differs from kernel to
+    // kernel and every kernel gives the same bits
+    auto madd = [](R a, R b, R c) { return sizeof(R) == 4 ? (R)__builtin_fmaf(a, b, c) : (R)__builtin_fma(a, b, c); };
+    auto scale = [&](cx<R> w) { return cx<R>{madd(k.re, w.re, -(k.im * w.im)), madd(k.re, w.im, k.im * w.re)}; };
+    m[6] = scale({c0.re - c1.re, c1.im - c0.im});
+    m[7] = scale({c2.re - c3.re, c3.im - c2.im});
+    m[8] = scale({c4.re - c5.re, c5.im - c4.im});
 }
 
 // ------------------------------------------------------------------ tracing
@@ -597,7 +601,8 @@ struct DslashLaunch {
     int block;
     int order;  // tile processing order: 0 memory order, 1 t-fastest planes,
                 // 2 | BY << 8 | BZ << 16 XCD bricks (dslash.hip); bits 24-25:
-                // log2 of the waves a site's RHS tiles are split over
+                // log2 of the waves a site's RHS tiles are split over; or a
+                // shared shape or SPLIT_ORDER, below
     int compressed;    // links in a compressed layout (CompMode)
     bool cached;       // one RHS per thread: links through the caches, not streamed
     const int *tiles;  // device, order of the 64-site tiles (link_tile_order); shared shapes only
@@ -624,5 +629,10 @@ inline int shared_order(int waves) { return 2 | (waves == 2 ? 1 : waves == 4 ? 2
 // The kernel's 32-bit byte offsets reach 2^28 sites of 16 bytes.
 inline bool shared_supported(const Geom &g) { return g.vh < (1 << 28); }
 int launch_dslash_shared(const Geom &g, const DslashLaunch &a, hipStream_t s);
+
+// Split shape (dslash_split.hip): order 4 without a K (the t-march has one), tile
+// 1, block 256: four wavefronts to 64 sites and one right-hand side.
+constexpr int SPLIT_ORDER = 4;
+int launch_dslash_split(const Geom &g, const DslashLaunch &a, hipStream_t s);  // -1: formats not built
 
 }  // namespace hisq

@@ -41,12 +41,20 @@ size_t dslash_algorithmic_bytes(int fl, int fi, int fo, int64_t vh, int nrhs, bo
 // Default launch shapes, by the measured times of the plain Dslash in a loop
 // (us, links cached where links_cached says so):
 //  * Few wavefronts (one per 64 sites and right-hand side, at most one per
-//    SIMD): one right-hand side per thread, all sixteen gathers in flight.  A
-//    shared launch, with its stages, takes longer: 8^4, FP32, 4 RHS 4.6
-//    against 5.6; 16^3 x 8, 4 RHS 5.9 against 6.3.  Not once the copies of the
-//    links that the XCDs fetch for different RHS crowd each other out of the
-//    L2s: 20^3 x 8, FP32, 2 RHS 12.4 against 8.4; 12^3 x 8, FP64, 2 RHS 11.8
-//    against 7.0.
+//    SIMD, FP16S two): one right-hand side per thread, all sixteen gathers in
+//    flight.  A shared launch, with its stages, takes longer: 8^4, FP32, 4 RHS
+//    4.6 against 5.6; 16^3 x 8, 4 RHS 5.9 against 6.3; so does an RHS tile in
+//    FP16S: 16^4, 4 RHS 9.2 against 13.5 (tile 4), 24^3 x 8, 2 RHS 9.7 against
+//    15.2 (tile 2), but 24^3 x 16 18.2 against 16.4.  Not once the copies of
+//    the links that the XCDs fetch for different RHS crowd each other out of
+//    the L2s: 20^3 x 8, FP32, 2 RHS 12.4 against 8.4; 12^3 x 8, FP64, 2 RHS
+//    11.8 against 7.0.
+//  * Fewer still, one workgroup of four wavefronts per CU (FP64) or two: the
+//    sixteen hops split over the four (kernel times, plain against split): FP64
+//    8^4 7.5 / 5.4, 16^3 x 8 12.6 / 9.2, but 16^4 14.2 / 14.5; FP32 8^4 5.5 /
+//    4.7, 16^3 x 8 with 2 RHS 7.4 / 6.6, 16^4 8.4 / 8.4, with whole links 11.4 /
+//    9.1, but 24^3 x 8 11.3 / 12.0; FP16S 8^4 5.7 / 4.6, 16^4 7.2 / 6.0, but
+//    24^3 x 8 8.4 / 9.2.
 //  * FP64 from 2, FP32 from 3 and FP16S from 5 right-hand sides: links shared
 //    through LDS, R = ceil(n / 4) per wavefront, at most 16 per workgroup.
 //    48^3 x 12 against the best other shape: FP64 n = 4 355 / 492, n = 16
@@ -61,12 +69,16 @@ DslashShape pick_shape(hisq_gauge_s *g, int fl, int fi, int fo, int nrhs, bool e
     if (it != g->shapes.end()) return it->second;
     DslashShape s;
     const int tiles = (g->geom.vh + 63) / 64;
-    const bool few = (int64_t)tiles * nrhs <= 1024 && tiles <= (fl == F64 ? 64 : fi == H16 ? 1024 : 256);
+    const int64_t waves1 = (int64_t)tiles * nrhs;  // with one right-hand side per wavefront
+    const bool few = waves1 <= (fi == H16 ? 2048 : 1024) && tiles <= (fl == F64 ? 64 : fi == H16 ? 1024 : 256);
     auto plain = [&](int tile, int block) {
         s.tile = tile;
         s.block = block;
     };
-    if (nrhs == 1) {
+    if (waves1 <= (fl == F64 ? 256 : 512) && (nrhs == 1 || few)) {
+        plain(1, 256);
+        s.order = SPLIT_ORDER;
+    } else if (nrhs == 1) {
         // measured on the 96^3 x 24 FP32 Dslash: 128-thread blocks are best for
         // one RHS; small lattices need the blocks (8^4, FP64: 5.7 against 5.9)
         plain(1, tiles < 2048 ? 64 : 128);
