@@ -38,8 +38,9 @@
 //     15.4 ms: each of ~20 waits was a round trip, and the sites in flight
 //     did not fit the L2 (T pass: 2.85 GB from beyond the L2, now 1.2 GB).
 // 48^3 x 12: 51 ms in 150 canonical-layout launches before, 13.2 ms now
-// (T 0.33, B 0.67, V 0.39 and 0.68 with Lepage, each 4 times per level);
-// 96^3 x 24: 840 ms before.
+// (T 0.33, B 0.67, V 0.39 and 0.68 with Lepage, each 4 times per level; 12.7 in
+// a later run);
+// 96^3 x 24: 840 ms before, 203 ms now.
 //
 // Scratch: the two outputs hold intermediate fields until their own pass
 // writes them, and one workspace of six one-direction fields comes on top:
