@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cstring>
+#include <utility>
 
 #include "nn_internal.h"
 
@@ -21,21 +22,33 @@ static NnGeom nn_geom(const hisq_gauge_s *g) {
 // one-channel even-site spinor, every other layer a hidden activation
 enum { MODE_HIDDEN = 0, MODE_EVEN = 1 };
 
-// Device buffers for `cap` training samples side by side; the old ones stay if
-// there is no memory for them (HISQ_ERR_OOM).
+// Device buffers for `cap` training samples side by side, in one block: a new
+// network's first step pays for every allocation.
 static int train_alloc(hisq_nn_s *n, int cap) {
     const NnGeom G = nn_geom(n->gauge);
     const size_t act = nn_act_bytes(G), sb = spinor_bytes(F32, G.V / 2);
     hisq_nn_s::Train &t = n->train;
     t.cap = 0;
-    for (DevBuf *b : {&t.act, &t.gbuf, &t.out, &t.gout, &t.partial, &t.red, &t.scal, &t.partd}) b->release();
-    int rc;
-    if ((rc = t.act.alloc(std::max<size_t>((n->nlayers - 1) * act * cap, 16))) || (rc = t.gbuf.alloc(2 * act * cap)) ||
-        (rc = t.out.alloc(sb * cap)) || (rc = t.gout.alloc(sb * cap)) ||
-        (rc = t.partial.alloc(nn_wgrad_partial_floats(G) * 4 * cap)) || (rc = t.red.alloc(n->nweights * 8 * cap)) ||
-        (rc = t.scal.alloc(8 * sizeof(double) * cap)) ||
-        (rc = t.partd.alloc(sizeof(double) * ((G.V / 2 + 255) / 256 + 1) * cap)))
-        return rc;
+    t.mem.release();
+    const std::pair<hisq_nn_s::Train::Part *, size_t> parts[] = {
+        {&t.act, std::max<size_t>((n->nlayers - 1) * act * cap, 16)},
+        {&t.gbuf, 2 * act * cap},
+        {&t.out, sb * cap},
+        {&t.gout, sb * cap},
+        {&t.partial, nn_wgrad_partial_floats(G) * 4 * cap},
+        {&t.red, n->nweights * 8 * cap},
+        {&t.scal, 8 * sizeof(double) * cap},
+        {&t.partd, sizeof(double) * ((G.V / 2 + 255) / 256 + 1) * cap}};
+    auto padded = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
+    size_t all = 0;
+    for (auto &p : parts) all += padded(p.second);
+    const int rc = t.mem.alloc(all);
+    if (rc) return rc;
+    char *at = (char *)t.mem.p;
+    for (auto &p : parts) {
+        p.first->p = at;
+        at += padded(p.second);
+    }
     t.cap = cap;
     return HISQ_OK;
 }

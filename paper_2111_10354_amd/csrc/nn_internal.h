@@ -52,9 +52,13 @@ struct hisq_nn_s {
     // buffers of `cap` training samples that go through the layers together
     struct Train {
         int cap = 0;
-        hisq::DevBuf act;   // activations of the hidden layers, [layer][sample]
-        hisq::DevBuf gbuf;  // back-propagated gradients, two of [sample]
-        hisq::DevBuf out, gout, partial, red, scal, partd;
+        hisq::DevBuf mem;  // holds all of the parts below
+        struct Part {
+            void *p = nullptr;
+        };
+        Part act;   // activations of the hidden layers, [layer][sample]
+        Part gbuf;  // back-propagated gradients, two of [sample]
+        Part out, gout, partial, red, scal, partd;
     } train;
     int step = 0;
     bool amat_valid = false;
