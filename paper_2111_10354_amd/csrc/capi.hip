@@ -233,8 +233,14 @@ int hisq_smear_links(const int dims[4], const double *thin, double *fat, double 
 
 int hisq_gauge_destroy(hisq_gauge_t g) {
     if (!g) return HISQ_OK;
-    if (hipDeviceSynchronize() == hipSuccess) g->recycle();
+    // the handle's device, which need not be the current one, has to be idle
+    // before its blocks may go to the next allocation there
+    const int device = g->device;
+    int current = device;
+    const bool there = hipGetDevice(&current) == hipSuccess && (current == device || hipSetDevice(device) == hipSuccess);
+    if (there && hipDeviceSynchronize() == hipSuccess) g->recycle();
     delete g;
+    if (current != device) (void)hipSetDevice(current);
     return HISQ_OK;
 }
 

@@ -1,0 +1,52 @@
+// Host code of libhisq.so against the stand-in runtime of host_runtime.h (no
+// GPU).  usage: host_runtime_check CASE; prints "ok", or what failed.
+#include "host_runtime.h"
+
+#include <vector>
+
+#include "hisq.h"
+#include "nn_internal.h"
+
+using namespace hisq;
+
+#define CHECK(cond)                                                       \
+    do {                                                                  \
+        if (!(cond)) {                                                    \
+            std::printf("FAILED line %d: %s\n", __LINE__, #cond);         \
+            std::exit(1);                                                 \
+        }                                                                 \
+    } while (0)
+
+static hisq_gauge_t make_gauge(const int dims[4], unsigned precs) {
+    static std::vector<double> links;  // zero: not compressible, small enough for FP16
+    const size_t V = (size_t)dims[0] * dims[1] * dims[2] * dims[3];
+    links.assign(V * 72, 0.0);
+    hisq_gauge_t g = nullptr;
+    CHECK(hisq_gauge_create(&g, dims, links.data(), links.data(), precs, nullptr) == HISQ_OK);
+    return g;
+}
+
+// A handle of device 1 destroyed while device 0 is current: its blocks must not
+// go to the next allocation there before device 1 has been waited for.
+static void destroy_other_device() {
+    const int dims[4] = {8, 8, 8, 8};
+    hipSetDevice(1);
+    hisq_gauge_t g = make_gauge(dims, HISQ_PREC_MASK(HISQ_PREC_FP32));
+    std::vector<char> in(spinor_bytes(F32, 2048) + 16), out(in.size());
+    auto align = [](std::vector<char> &v) { return (void *)(((uintptr_t)v.data() + 15) & ~(uintptr_t)15); };
+    CHECK(hisq_dslash_eo(g, 0, HISQ_PREC_FP32, align(in), align(out), nullptr) == HISQ_OK);
+    CHECK(fake::pending[1] > 0);
+    hipSetDevice(0);
+    CHECK(hisq_gauge_destroy(g) == HISQ_OK);
+    int dev = -1;
+    CHECK(hipGetDevice(&dev) == hipSuccess && dev == 0);
+    CHECK(fake::pending[1] == 0);
+}
+
+int main(int argc, char **argv) {
+    const std::string c = argc > 1 ? argv[1] : "";
+    if (c == "destroy_other_device") destroy_other_device();
+    else CHECK(!"a known case");
+    std::printf("ok\n");
+    return 0;
+}
