@@ -93,10 +93,12 @@ int DevBuf::alloc(size_t n) {
         if (e == hipErrorOutOfMemory) {
             std::lock_guard<std::mutex> lk(k.mu);
             if (!k.blocks.empty()) {
-                (void)hipGetLastError();
                 while (!k.blocks.empty()) k.drop(k.blocks.begin());
                 e = hipMalloc(&p, n);
             }
+            // The runtime keeps a failed call's error until it is asked for it:
+            // the check after the next launch must not find these.
+            (void)hipGetLastError();
         }
         if (e != hipSuccess) {
             p = nullptr;

@@ -43,9 +43,28 @@ static void destroy_other_device() {
     CHECK(fake::pending[1] == 0);
 }
 
+// An allocation that fails, with or without kept blocks to give up, leaves no
+// error behind: the next launch check is not the one to report it.
+static void failed_allocation() {
+    for (int kept = 0; kept < 2; ++kept) {
+        if (kept) {
+            DevBuf k;
+            CHECK(k.alloc(1 << 20) == HISQ_OK);
+            k.recycle();
+        }
+        fake::max_block = 1 << 21;
+        DevBuf b;
+        CHECK(b.alloc(1 << 22) == HISQ_ERR_OOM);
+        CHECK(hipGetLastError() == hipSuccess);
+        fake::max_block = ~(size_t)0;
+        CHECK(b.alloc(1 << 22) == HISQ_OK);
+    }
+}
+
 int main(int argc, char **argv) {
     const std::string c = argc > 1 ? argv[1] : "";
     if (c == "destroy_other_device") destroy_other_device();
+    else if (c == "failed_allocation") failed_allocation();
     else CHECK(!"a known case");
     std::printf("ok\n");
     return 0;
