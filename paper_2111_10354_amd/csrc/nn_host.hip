@@ -23,13 +23,12 @@ static NnGeom nn_geom(const hisq_gauge_s *g) {
 enum { MODE_HIDDEN = 0, MODE_EVEN = 1 };
 
 // Device buffers for `cap` training samples side by side, in one block: a new
-// network's first step pays for every allocation.
+// network's first step pays for every allocation.  The buffers that the network
+// has are given up only for others: training goes on where these cannot be had.
 static int train_alloc(hisq_nn_s *n, int cap) {
     const NnGeom G = nn_geom(n->gauge);
     const size_t act = nn_act_bytes(G), sb = spinor_bytes(F32, G.V / 2);
     hisq_nn_s::Train &t = n->train;
-    t.cap = 0;
-    t.mem.release();
     const std::pair<hisq_nn_s::Train::Part *, size_t> parts[] = {
         {&t.act, std::max<size_t>((n->nlayers - 1) * act * cap, 16)},
         {&t.gbuf, 2 * act * cap},
@@ -42,14 +41,30 @@ static int train_alloc(hisq_nn_s *n, int cap) {
     auto padded = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
     size_t all = 0;
     for (auto &p : parts) all += padded(p.second);
-    const int rc = t.mem.alloc(all);
+    DevBuf mem;
+    const int rc = mem.alloc(all);
     if (rc) return rc;
+    t.mem.swap(mem);
     char *at = (char *)t.mem.p;
     for (auto &p : parts) {
         p.first->p = at;
         at += padded(p.second);
     }
     t.cap = cap;
+    return HISQ_OK;
+}
+
+// Makes room for groups of `want` samples, or of as many as memory allows: half
+// as many after each refusal.  A batch that memory did not suffice for, or a
+// larger one, does not ask again.
+static int train_reserve(hisq_nn_s *n, int want) {
+    hisq_nn_s::Train &t = n->train;
+    if (want <= t.cap || want >= t.refused) return HISQ_OK;
+    for (int m = want; m > t.cap; m /= 2) {
+        const int rc = train_alloc(n, m);
+        if (rc != HISQ_ERR_OOM) return rc;
+        t.refused = want;
+    }
     return HISQ_OK;
 }
 
@@ -153,12 +168,7 @@ int nn_loss_grad_batch(hisq_nn_s *n, int batch, const float *av, const float *v,
     const int vh = G.V / 2, L = n->nlayers;
     const size_t sb = spinor_bytes(F32, vh), act = nn_act_bytes(G);
     int rc;
-    const int want = train_group(n, batch);
-    if (want > n->train.cap) {
-        rc = train_alloc(n, want);
-        if (rc == HISQ_ERR_OOM) rc = train_alloc(n, 1);
-        if (rc) return rc;
-    }
+    if ((rc = train_reserve(n, train_group(n, batch)))) return rc;
     HISQ_HIP_CHECK(hipMemsetAsync(n->g.p, 0, n->nweights * 8, s));
     HISQ_HIP_CHECK(hipMemsetAsync(n->scal.p, 0, 8 * sizeof(double), s));
     if (!n->amat_valid) build_amats(n, s);

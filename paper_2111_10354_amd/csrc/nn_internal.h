@@ -1,6 +1,7 @@
 // Host-side structures of the preconditioner network.
 #pragma once
 
+#include <climits>
 #include <vector>
 
 #include "solver_internal.h"
@@ -52,6 +53,7 @@ struct hisq_nn_s {
     // buffers of `cap` training samples that go through the layers together
     struct Train {
         int cap = 0;
+        int refused = INT_MAX;  // smallest group that there was no memory for
         hisq::DevBuf mem;  // holds all of the parts below
         struct Part {
             void *p = nullptr;

@@ -6,6 +6,7 @@
 #include <memory>
 #include <mutex>
 #include <tuple>
+#include <utility>
 #include <vector>
 
 #include "hisq_internal.h"
@@ -90,6 +91,12 @@ struct DevBuf {
     int alloc(size_t n);
     void release();
     void recycle();
+    void swap(DevBuf &o) {
+        std::swap(p, o.p);
+        std::swap(bytes, o.bytes);
+        std::swap(held, o.held);
+        std::swap(device, o.device);
+    }
 };
 
 // Recycles buffers of a call that has waited for its stream.

@@ -43,6 +43,41 @@ static void destroy_other_device() {
     CHECK(fake::pending[1] == 0);
 }
 
+// Training where memory for one sample's buffers is there and for a whole
+// batch's is not: the batch trains, larger blocks are not asked for again and
+// again, no failed allocation is left as the thread's last error, and the
+// buffers that the network has are never given up for larger ones.
+static void training_without_memory() {
+    const int dims[4] = {8, 8, 8, 8}, ch[4] = {1, 8, 8, 1};
+    hisq_gauge_t g = make_gauge(dims, HISQ_PREC_MASK(HISQ_PREC_FP32));
+    std::vector<double> thin(4096 * 72, 0.0);
+    CHECK(hisq_gauge_set_thin(g, thin.data(), nullptr) == HISQ_OK);
+    hisq_nn_t net = nullptr;
+    CHECK(hisq_nn_create(&net, g, 3, ch, nullptr, nullptr) == HISQ_OK);
+    std::vector<float> v(8 * 6 * 2048 + 4, 0.f);
+    double loss = -1.0;
+    const size_t have = net->train.mem.bytes;
+    CHECK(net->train.cap == 1 && have > 0);
+    fake::max_block = have;
+    for (int k = 0; k < 3; ++k) {
+        CHECK(hisq_nn_loss_grad(net, 8, v.data(), v.data(), &loss, nullptr, nullptr) == HISQ_OK);
+        CHECK(hisq_nn_train_step(net, 8, v.data(), v.data(), 1e-3, &loss, nullptr) == HISQ_OK);
+        CHECK(net->train.mem.bytes >= have);
+    }
+    const long refused = fake::refused;
+    CHECK(hisq_nn_loss_grad(net, 8, v.data(), v.data(), &loss, nullptr, nullptr) == HISQ_OK);
+    CHECK(fake::refused == refused);
+    fake::max_block = 3 * have;  // a smaller batch may ask again
+    CHECK(hisq_nn_loss_grad(net, 3, v.data(), v.data(), &loss, nullptr, nullptr) == HISQ_OK);
+    CHECK(net->train.cap >= 2);
+    const size_t grown = net->train.mem.bytes;
+    fake::max_block = 0;  // nothing: the buffers stay
+    CHECK(hisq_nn_loss_grad(net, 8, v.data(), v.data(), &loss, nullptr, nullptr) == HISQ_OK);
+    CHECK(net->train.mem.bytes == grown);
+    fake::max_block = ~(size_t)0;
+    CHECK(hisq_nn_destroy(net) == HISQ_OK && hisq_gauge_destroy(g) == HISQ_OK);
+}
+
 // An allocation that fails, with or without kept blocks to give up, leaves no
 // error behind: the next launch check is not the one to report it.
 static void failed_allocation() {
@@ -64,6 +99,7 @@ static void failed_allocation() {
 int main(int argc, char **argv) {
     const std::string c = argc > 1 ? argv[1] : "";
     if (c == "destroy_other_device") destroy_other_device();
+    else if (c == "training_without_memory") training_without_memory();
     else if (c == "failed_allocation") failed_allocation();
     else CHECK(!"a known case");
     std::printf("ok\n");
