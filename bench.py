@@ -54,15 +54,17 @@ def encode(cb, prec):
 
 def counter_traffic(dims, compressed, shape):
     """HBM bytes per launch of the headline kernel from the committed rocprofv3
-    counter summary, or None if the kernel sources, the link layout or the
-    launch shape (RHS tile, block, tile order) changed since it was taken."""
+    counter summary, or None if the sources of the kernel, its dispatch and its
+    links (streamed or cached among them), the link layout or the launch shape
+    (RHS tile, block, tile order) changed since it was taken."""
     import hashlib
     path = os.path.join(ROOT, "profiles", f"dslash_fp32_{'x'.join(map(str, dims))}.traffic.json")
     if not os.path.exists(path):
         return None
     rec = json.load(open(path))
     csrc = os.path.join(ROOT, "paper_2111_10354_amd", "csrc")
-    src = b"".join(open(os.path.join(csrc, n), "rb").read() for n in ("dslash.hip", "hisq_internal.h", "pack.hip"))
+    src = b"".join(open(os.path.join(csrc, n), "rb").read()
+                   for n in ("dslash.hip", "dslash_kernel.h", "dslash_f32.hip", "hisq_internal.h", "pack.hip"))
     if hashlib.sha256(src).hexdigest() != rec.get("kernel_sources_sha256"):
         return None
     if bool(rec.get("long_links_compressed", False)) != bool(compressed):

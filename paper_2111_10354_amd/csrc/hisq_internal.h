@@ -356,6 +356,13 @@ __host__ __device__ __forceinline__ const u4v *link_unit_ptr(const void *base, i
     return (const u4v *)base + ((size_t)((h >> 6) * ng + gi) * 9) * 64 + (h & 63);
 }
 
+// Links of a launch go through the caches where both parities' fit the 256 MiB
+// Infinity Cache, and past them otherwise.  One RHS, links through / past the
+// caches: 12^3 x 8 FP64 5.8 / 12.2 us, 16^3 x 8 FP32 4.8 / 9.2, 24^3 x 8 FP32
+// 11.1 / 13.3, 32^3 x 8 FP32 (241 MiB) 21.0 / 22.0, FP64 (576 MiB) 51.2 / 50.6,
+// 48^3 x 12 FP32 (1.2 GiB) 129 / 119.
+inline bool links_fit_caches(size_t parity_bytes) { return parity_bytes <= ((size_t)128 << 20); }
+
 // Link loads: non-temporal (streamed past the caches) when each link byte is
 // read once per launch; cached when several waves of a workgroup read the same
 // links (the RHS of a site split over waves).

@@ -103,12 +103,7 @@ DslashShape pick_shape(hisq_gauge_s *g, int fl, int fi, int fo, int nrhs, bool e
     return s;
 }
 
-// Links of a launch go through the caches where both parities' fit the 256 MiB
-// Infinity Cache, and past them otherwise.  One RHS, links through / past the
-// caches: 12^3 x 8 FP64 5.8 / 12.2 us, 16^3 x 8 FP32 4.8 / 9.2, 24^3 x 8 FP32
-// 11.1 / 13.3, 32^3 x 8 FP32 (241 MiB) 21.0 / 22.0, FP64 (576 MiB) 51.2 / 50.6,
-// 48^3 x 12 FP32 (1.2 GiB) 129 / 119.
-bool links_cached(const hisq_gauge_s *g, int fl) { return g->links[fl][0].bytes <= ((size_t)128 << 20); }
+bool links_cached(const hisq_gauge_s *g, int fl) { return links_fit_caches(g->links[fl][0].bytes); }
 
 static int dslash_on(hisq_gauge_s *g, int out_parity, int fl, int fi, int fo, int nrhs, const void *in, void *out,
                      const void *y, const Coefs *diag, double *partials, const CgState *skip, hipStream_t s) {
