@@ -63,10 +63,11 @@ def counter_traffic(dims, compressed, shape):
         return None
     rec = json.load(open(path))
     csrc = os.path.join(ROOT, "paper_2111_10354_amd", "csrc")
-    src = b"".join(open(os.path.join(csrc, n), "rb").read()
-                   for n in ("dslash.hip", "dslash_kernel.h", "dslash_f32.hip", "hisq_internal.h", "pack.hip"))
-    if hashlib.sha256(src).hexdigest() != rec.get("kernel_sources_sha256"):
-        return None
+    for key, names in (("kernel_sources_sha256", ("dslash.hip", "hisq_internal.h", "pack.hip")),
+                       ("kernel_instances_sha256", ("dslash_kernel.h", "dslash_f32.hip"))):
+        src = b"".join(open(os.path.join(csrc, n), "rb").read() for n in names)
+        if hashlib.sha256(src).hexdigest() != rec.get(key):
+            return None
     if bool(rec.get("long_links_compressed", False)) != bool(compressed):
         return None
     if rec.get("launch_shape") != [int(v) for v in shape]:
