@@ -39,12 +39,12 @@
  * never frees them and keeps no reference after a call returns.  A gauge handle
  * owns the library's own packed link copies and solver workspaces.  Memory of
  * destroyed handles and finished calls is kept for the library's next
- * allocations: at most 16 GiB, freed when an allocation of the library fails
- * and, if nobody wanted it for five seconds, by the next call that allocates.
- * `stream`
- * is a hipStream_t (NULL = the default stream).  Dslash calls are asynchronous
- * on that stream; solvers order themselves after prior work on it and return
- * when x is written (synchronous).
+ * allocations: at most 16 GiB, freed when an allocation of the library fails,
+ * if nobody wanted it for five seconds by the next call that allocates, and by
+ * hisq_release_memory, which a program calls before it needs nearly all of the
+ * device for itself.  `stream` is a hipStream_t (NULL = the default stream).
+ * Dslash calls are asynchronous on that stream; solvers order themselves after
+ * prior work on it and return when x is written (synchronous).
  *
  * Errors: 0 = OK.  Negative = hard error (nothing usable was written):
  *   -1 invalid argument, -2 HIP runtime error, -3 out of device memory,
@@ -92,8 +92,9 @@ typedef struct hisq_nn_s *hisq_nn_t;
 /* Library version (major*10000 + minor*100 + patch); equals HISQ_VERSION of
  * the header the library was built with.  0.2.0: hisq_solver_params gained
  * ru_delta (callers built against 0.1 pass a shorter struct).  0.3.0:
- * hisq_multishift_cg_batched and hisq_rational_apply_batched. */
-#define HISQ_VERSION 300
+ * hisq_multishift_cg_batched and hisq_rational_apply_batched.  0.3.1:
+ * hisq_release_memory. */
+#define HISQ_VERSION 301
 int hisq_version(void);
 
 /* Message describing the calling thread's most recent error ("" if none). */
@@ -166,6 +167,12 @@ int hisq_gauge_links_compressed(hisq_gauge_t g);
 
 /* Release the handle and everything it owns (NULL is accepted). */
 int hisq_gauge_destroy(hisq_gauge_t g);
+
+/* Give the memory that the library keeps of destroyed handles and finished
+ * calls back to the device; *bytes (may be NULL) is how much it was.  Memory
+ * of live handles and networks stays.  -2: the runtime refused some of it (as
+ * while a thread captures a graph), which stays kept. */
+int hisq_release_memory(size_t *bytes);
 
 /* Bytes of device memory owned by the handle (packed links plus workspaces). */
 int hisq_gauge_device_bytes(hisq_gauge_t g, size_t *bytes);

@@ -250,6 +250,8 @@ int hisq_gauge_links_compressed(hisq_gauge_t g) {
     return g->comp_mode;
 }
 
+int hisq_release_memory(size_t *bytes) { return release_kept(bytes); }
+
 int hisq_gauge_device_bytes(hisq_gauge_t g, size_t *bytes) {
     int rc = check_handle(g);
     if (rc) return rc;

@@ -13,10 +13,14 @@
 //   * the list is bounded (kKeepBytes in all, kKeepBlocks), the oldest blocks
 //     leaving first; a block over the bound is freed at once;
 //   * a block that nobody wanted for kKeepSeconds is freed by the next call
-//     that allocates or recycles, and all are freed when an allocation fails.
+//     that allocates or recycles, and all are freed when an allocation fails
+//     or the program asks for it (release_kept);
+//   * the list is a fixed array: giving a block back allocates nothing and
+//     cannot fail.
 
+#include <algorithm>
 #include <chrono>
-#include <list>
+#include <new>
 
 #include "solver_internal.h"
 
@@ -34,46 +38,78 @@ struct Block {
 };
 
 constexpr size_t kKeepBytes = (size_t)16 << 30;  // 6 % of the device
-constexpr size_t kKeepBlocks = 256;
+constexpr int kKeepBlocks = 256;
 constexpr double kKeepSeconds = 5.0;
 
 struct Kept {
     std::mutex mu;
-    std::list<Block> blocks;  // oldest first
+    Block blocks[kKeepBlocks];  // the first n, oldest first
+    int n = 0;
     size_t total = 0;
 
-    void drop(std::list<Block>::iterator it) {
-        total -= it->bytes;
-        (void)hipFree(it->p);
-        blocks.erase(it);
+    void remove(int i) {
+        total -= blocks[i].bytes;
+        std::copy(blocks + i + 1, blocks + n, blocks + i);
+        --n;
+    }
+    // false: the runtime refuses (while a thread captures a graph): the block stays
+    bool drop(int i) {
+        if (hipFree(blocks[i].p) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        remove(i);
+        return true;
     }
     void drop_old(Clock::time_point now) {
-        while (!blocks.empty() && std::chrono::duration<double>(now - blocks.front().since).count() > kKeepSeconds)
-            drop(blocks.begin());
+        while (n > 0 && std::chrono::duration<double>(now - blocks[0].since).count() > kKeepSeconds && drop(0)) {
+        }
     }
-    // the smallest block of n to 9/8 n bytes (nullptr if none)
-    void *take(size_t n, int device, size_t *bytes) {
-        auto best = blocks.end();
-        for (auto it = blocks.begin(); it != blocks.end(); ++it)
-            if (it->device == device && it->bytes >= n && it->bytes - n <= n / 8 &&
-                (best == blocks.end() || it->bytes < best->bytes))
-                best = it;
-        if (best == blocks.end()) return nullptr;
-        void *p = best->p;
-        *bytes = best->bytes;
-        total -= best->bytes;
-        blocks.erase(best);
+    bool drop_all() {
+        while (n > 0 && drop(n - 1)) {
+        }
+        return n == 0;
+    }
+    // room for a block of b <= kKeepBytes bytes
+    bool make_room(size_t b) {
+        while (n > 0 && (total + b > kKeepBytes || n >= kKeepBlocks))
+            if (!drop(0)) return false;
+        return true;
+    }
+    // the smallest block of b to 9/8 b bytes (nullptr if none)
+    void *take(size_t b, int device, size_t *bytes) {
+        int best = -1;
+        for (int i = 0; i < n; ++i)
+            if (blocks[i].device == device && blocks[i].bytes >= b && blocks[i].bytes - b <= b / 8 &&
+                (best < 0 || blocks[i].bytes < blocks[best].bytes))
+                best = i;
+        if (best < 0) return nullptr;
+        void *p = blocks[best].p;
+        *bytes = blocks[best].bytes;
+        remove(best);
         return p;
     }
 };
 
 // Never destroyed: the HIP runtime may be gone when static destructors run.
 Kept &kept() {
-    static Kept *k = new Kept();
+    alignas(Kept) static unsigned char mem[sizeof(Kept)];
+    static Kept *k = new (mem) Kept();
     return *k;
 }
 
 }  // namespace
+
+int release_kept(size_t *bytes) {
+    Kept &k = kept();
+    std::lock_guard<std::mutex> lk(k.mu);
+    const size_t before = k.total;
+    const bool all = k.drop_all();
+    if (bytes) *bytes = before - k.total;
+    if (all) return HISQ_OK;
+    set_error("kept device memory could not be freed");
+    return HISQ_ERR_HIP;
+}
 
 int DevBuf::alloc(size_t n) {
     if (p && bytes >= n) return HISQ_OK;
@@ -92,8 +128,8 @@ int DevBuf::alloc(size_t n) {
         hipError_t e = hipMalloc(&p, n);
         if (e == hipErrorOutOfMemory) {
             std::lock_guard<std::mutex> lk(k.mu);
-            if (!k.blocks.empty()) {
-                while (!k.blocks.empty()) k.drop(k.blocks.begin());
+            if (k.n > 0) {
+                (void)k.drop_all();
                 e = hipMalloc(&p, n);
             }
             // The runtime keeps a failed call's error until it is asked for it:
@@ -123,9 +159,8 @@ void DevBuf::recycle() {
     const auto now = Clock::now();
     {
         std::lock_guard<std::mutex> lk(k.mu);
-        while (!k.blocks.empty() && (k.total + held > kKeepBytes || k.blocks.size() >= kKeepBlocks))
-            k.drop(k.blocks.begin());
-        k.blocks.push_back({p, held, device, now});
+        if (!k.make_room(held)) return release();
+        k.blocks[k.n++] = {p, held, device, now};
         k.total += held;
         k.drop_old(now);
     }

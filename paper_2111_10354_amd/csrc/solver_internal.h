@@ -99,6 +99,9 @@ struct DevBuf {
     }
 };
 
+// Frees every kept block (hisq_release_memory).
+int release_kept(size_t *bytes);
+
 // Recycles buffers of a call that has waited for its stream.
 template <class... B>
 inline void recycle_all(B &...b) {

@@ -58,6 +58,7 @@ def _load():
         "hisq_spinor_bytes": (C.c_size_t, [C.c_int, C.c_int64]),
         "hisq_gauge_create": (C.c_int, [C.POINTER(vp), ip, vp, vp, C.c_uint, vp]),
         "hisq_gauge_destroy": (C.c_int, [vp]),
+        "hisq_release_memory": (C.c_int, [C.POINTER(C.c_size_t)]),
         "hisq_gauge_device_bytes": (C.c_int, [vp, C.POINTER(C.c_size_t)]),
         "hisq_dslash_eo": (C.c_int, [vp, C.c_int, C.c_int, vp, vp, vp]),
         "hisq_dslash_multi_rhs": (C.c_int, [vp, C.c_int, C.c_int, C.c_int, vp, vp, dp, vp, vp]),
@@ -108,7 +109,7 @@ EXPORTS = ("hisq_version", "hisq_last_error", "hisq_spinor_bytes", "hisq_gauge_c
            "hisq_nn_train_step", "hisq_gauge_links_compressed", "hisq_rational_apply",
            "hisq_zolotarev_inv_sqrt", "hisq_rational_remez", "hisq_spectral_bounds",
            "hisq_dslash_multi_rhs_noalloc", "hisq_smear_links", "hisq_multishift_cg_batched",
-           "hisq_rational_apply_batched")
+           "hisq_rational_apply_batched", "hisq_release_memory")
 
 LINKS_FULL = 1 << 8  # hisq_gauge_create: store every link whole
 
@@ -155,6 +156,14 @@ def _need(t, nbytes: int, what: str):
 
 def version() -> int:
     return LIB.hisq_version()
+
+
+def release_memory() -> int:
+    """Gives the memory kept of closed handles and finished calls back to the
+    device; returns the bytes."""
+    n = C.c_size_t()
+    _check(LIB.hisq_release_memory(C.byref(n)))
+    return n.value
 
 
 def spinor_bytes(prec, vh: int) -> int:

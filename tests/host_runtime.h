@@ -49,9 +49,9 @@ inline void *take(size_t n) {  // large blocks are address space only
     return p == MAP_FAILED ? nullptr : p;
 }
 
+// A small block is not given back, so that no two blocks ever have one address.
 inline void give(void *p, size_t n) {
-    if (n < ((size_t)1 << 28)) std::free(p);
-    else munmap(p, n);
+    if (n >= ((size_t)1 << 28)) munmap(p, n);
 }
 
 }  // namespace fake

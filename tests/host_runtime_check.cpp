@@ -96,10 +96,107 @@ static void failed_allocation() {
     }
 }
 
+// The list of kept blocks: what it hands on, and when it frees.
+static void kept_blocks() {
+    const size_t M = 1 << 20;
+    auto keep = [](size_t n) {
+        DevBuf b;
+        CHECK(b.alloc(n) == HISQ_OK);
+        void *p = b.p;
+        b.recycle();
+        CHECK(!b.p && !b.bytes);
+        return p;
+    };
+    // a block goes to an allocation of 8/9 of its size to its own, on its device
+    void *p = keep(9 * M);
+    const long mallocs = fake::mallocs;
+    {
+        DevBuf a, b, c;
+        CHECK(a.alloc(8 * M - 1) == HISQ_OK && a.p != p);
+        CHECK(b.alloc(9 * M + 1) == HISQ_OK && b.p != p);
+        hipSetDevice(1);
+        CHECK(c.alloc(9 * M) == HISQ_OK && c.p != p);
+        hipSetDevice(0);
+        CHECK(fake::mallocs == mallocs + 3);
+        DevBuf d;
+        CHECK(d.alloc(8 * M) == HISQ_OK && d.p == p && d.bytes == 8 * M && fake::mallocs == mallocs + 3);
+        d.recycle();
+        CHECK(d.alloc(9 * M) == HISQ_OK && d.p == p);  // still the whole block
+    }
+    // the smallest of several that fit
+    {
+        void *large = keep(10 * M);
+        DevBuf s;
+        CHECK(s.alloc(9 * M + M / 2) == HISQ_OK && s.p == large);
+        DevBuf t;
+        CHECK(t.alloc(9 * M + M / 4) == HISQ_OK);
+        void *small = t.p;
+        s.recycle();
+        t.recycle();
+        DevBuf u;
+        CHECK(u.alloc(9 * M) == HISQ_OK && u.p == small);
+    }
+    size_t freed = 0;
+    CHECK(hisq_release_memory(&freed) == HISQ_OK && freed == 10 * M);
+    CHECK(hisq_release_memory(&freed) == HISQ_OK && freed == 0 && fake::blocks.empty());
+
+    // at most 16 GiB and 256 blocks, the oldest leaving first; larger ones at once
+    const size_t G = (size_t)1 << 30;
+    keep(17 * G);
+    CHECK(fake::total == 0);
+    void *first = keep(3 * G);
+    void *second = keep(6 * G);
+    void *third = keep(9 * G);
+    CHECK(!fake::blocks.count(first) && fake::blocks.count(second) && fake::blocks.count(third));
+    CHECK(hisq_release_memory(nullptr) == HISQ_OK && fake::total == 0);
+    {
+        std::vector<DevBuf> many(257);
+        for (auto &b : many) CHECK(b.alloc(4096) == HISQ_OK);
+        first = many[0].p;
+        second = many[1].p;
+        for (auto &b : many) b.recycle();
+    }
+    CHECK(fake::blocks.size() == 256 && !fake::blocks.count(first) && fake::blocks.count(second));
+    CHECK(hisq_release_memory(nullptr) == HISQ_OK && fake::total == 0);
+
+    // after five seconds the next call that allocates or recycles frees it
+    p = keep(M);
+    fake::clock_shift += 4.0;
+    keep(2 * M);
+    CHECK(fake::blocks.count(p));
+    fake::clock_shift += 2.0;
+    DevBuf b;
+    CHECK(b.alloc(64) == HISQ_OK && !fake::blocks.count(p) && fake::total == 2 * M + 64);
+    fake::clock_shift += 6.0;
+    b.recycle();
+    CHECK(fake::total == 64);
+
+    // a failing allocation takes everything that is kept
+    p = keep(4 * M);
+    fake::budget = 6 * M;
+    CHECK(b.alloc(5 * M) == HISQ_OK && !fake::blocks.count(p) && fake::total == 5 * M);
+    CHECK(hipGetLastError() == hipSuccess);
+    fake::budget = ~(size_t)0;
+    b.release();
+    CHECK(fake::total == 0);
+
+    // a block that the runtime does not free now is not lost
+    keep(M);
+    fake::free_fails = true;
+    CHECK(hisq_release_memory(&freed) == HISQ_ERR_HIP && freed == 0);
+    fake::clock_shift += 6.0;
+    CHECK(b.alloc(64) == HISQ_OK && hipGetLastError() == hipSuccess);
+    fake::free_fails = false;
+    CHECK(hisq_release_memory(&freed) == HISQ_OK && freed == M);
+    b.release();
+    CHECK(fake::total == 0);
+}
+
 int main(int argc, char **argv) {
     const std::string c = argc > 1 ? argv[1] : "";
     if (c == "destroy_other_device") destroy_other_device();
     else if (c == "training_without_memory") training_without_memory();
+    else if (c == "kept_blocks") kept_blocks();
     else if (c == "failed_allocation") failed_allocation();
     else CHECK(!"a known case");
     std::printf("ok\n");
