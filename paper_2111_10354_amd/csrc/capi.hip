@@ -192,14 +192,19 @@ int hisq_gauge_create(hisq_gauge_t *out, const int dims[4], const double *fat, c
     }
     e = hipStreamCreateWithFlags(&g->capture_stream, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&g->diag_event, hipEventDisableTiming);
-    std::vector<int> order((g->geom.vh + 63) / 64);  // lives until the stream is waited for below
+    const size_t tiles = (g->geom.vh + 63) / 64;
+    std::unique_ptr<int[]> order(new (std::nothrow) int[tiles]);  // lives until the stream is waited for below
     if (e == hipSuccess) {
-        link_tile_order(g->geom, order.data());
-        if ((rc = g->tile_order.alloc(sizeof(int) * order.size()))) {
+        if (!order) {
+            delete g;
+            return fail(HISQ_ERR_OOM, "host allocation failed");
+        }
+        link_tile_order(g->geom, order.get());
+        if ((rc = g->tile_order.alloc(sizeof(int) * tiles))) {
             delete g;
             return rc;
         }
-        e = hipMemcpyAsync(g->tile_order.p, order.data(), sizeof(int) * order.size(), hipMemcpyHostToDevice, s);
+        e = hipMemcpyAsync(g->tile_order.p, order.get(), sizeof(int) * tiles, hipMemcpyHostToDevice, s);
     }
     // epilogue coefficients of up to 64 right-hand sides without a later allocation
     if (e == hipSuccess && (rc = g->diag_buf.alloc(sizeof(double) * 64))) {

@@ -2,6 +2,8 @@
 // GPU).  usage: host_runtime_check CASE; prints "ok", or what failed.
 #include "host_runtime.h"
 
+#include <new>
+#include <string>
 #include <vector>
 
 #include "hisq.h"
@@ -192,10 +194,38 @@ static void kept_blocks() {
     CHECK(fake::total == 0);
 }
 
+// Host memory that runs out in hisq_gauge_create is an error code, not an exception.
+static size_t largest_new = ~(size_t)0;
+void *operator new(size_t n) {
+    void *p = n <= largest_new ? std::malloc(n) : nullptr;
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void *operator new(size_t n, const std::nothrow_t &) noexcept { return n <= largest_new ? std::malloc(n) : nullptr; }
+void *operator new[](size_t n) { return operator new(n); }
+void *operator new[](size_t n, const std::nothrow_t &t) noexcept { return operator new(n, t); }
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+void operator delete[](void *p) noexcept { std::free(p); }
+void operator delete[](void *p, size_t) noexcept { std::free(p); }
+
+static void create_without_host_memory() {
+    const int dims[4] = {96, 96, 96, 24};
+    const double *links = (const double *)0x10000;  // read by kernels only
+    hisq_gauge_t g = nullptr;
+    largest_new = 1 << 16;
+    CHECK(hisq_gauge_create(&g, dims, links, links, HISQ_PREC_MASK(HISQ_PREC_FP32), nullptr) == HISQ_ERR_OOM && !g);
+    CHECK(hisq_release_memory(nullptr) == HISQ_OK && fake::blocks.empty());
+    largest_new = ~(size_t)0;
+    CHECK(hisq_gauge_create(&g, dims, links, links, HISQ_PREC_MASK(HISQ_PREC_FP32), nullptr) == HISQ_OK);
+    CHECK(hisq_gauge_destroy(g) == HISQ_OK);
+}
+
 int main(int argc, char **argv) {
     const std::string c = argc > 1 ? argv[1] : "";
     if (c == "destroy_other_device") destroy_other_device();
     else if (c == "training_without_memory") training_without_memory();
+    else if (c == "create_without_host_memory") create_without_host_memory();
     else if (c == "kept_blocks") kept_blocks();
     else if (c == "failed_allocation") failed_allocation();
     else CHECK(!"a known case");
