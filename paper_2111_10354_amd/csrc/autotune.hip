@@ -214,7 +214,7 @@ int tune_dslash(hisq_gauge_s *g, int fl, int fi, int fo, int nrhs, bool epi, con
     ref_shape.order = 0;
     if ((rc = launch(ref_shape, ref.p))) return rc;
 
-    std::vector<DslashShape> cands;
+    std::vector<DslashShape> cands{default_shape(g, fl, fi, nrhs)};  // never to be replaced by a slower one
     for (int rsl = 0; rsl <= 2; ++rsl)  // RHS tiles of a site on 1, 2 or 4 waves
         for (int tile : {1, 2, 4, 8, 16})
             for (int block : {64, 128, 256})
@@ -244,7 +244,7 @@ int tune_dslash(hisq_gauge_s *g, int fl, int fi, int fo, int nrhs, bool epi, con
             if (valid_shape(G, fl, nrhs, c)) cands.push_back(c);
         }
 
-    if (nrhs * ((G.vh + 63) / 64) <= 2048) {  // the hops of few sites split over four waves
+    if ((int64_t)nrhs * ((G.vh + 63) / 64) <= 2048) {  // the hops of few sites split over four waves
         DslashShape c;
         c.tile = 1;
         c.block = 256;
@@ -254,7 +254,7 @@ int tune_dslash(hisq_gauge_s *g, int fl, int fi, int fo, int nrhs, bool epi, con
 
     for (int tile : {1, 2, 3, 4})  // links shared through LDS by the waves of a site tile
         for (int waves : {2, 3, 4}) {
-            if (waves == 3 && nrhs <= 4) continue;
+            if (waves == 3 && nrhs == 4) continue;  // three and one
             DslashShape c;
             c.tile = tile;
             c.block = 64 * waves;

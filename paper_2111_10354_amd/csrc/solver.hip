@@ -64,9 +64,7 @@ size_t dslash_algorithmic_bytes(int fl, int fi, int fo, int64_t vh, int nrhs, bo
 //    wavefront, which more RHS per thread spread: 48^3 x 12, n = 4 110 (tile 4)
 //    against 127; FP32 n = 2 132 (tile 2) against 138, while a small lattice
 //    gains from twice the wavefronts (24^3 x 8: 12.2 shared, 13.1 tile 2).
-DslashShape pick_shape(hisq_gauge_s *g, int fl, int fi, int fo, int nrhs, bool epi) {
-    auto it = g->shapes.find(std::make_tuple(fl, fi, fo, nrhs, (int)epi));
-    if (it != g->shapes.end()) return it->second;
+DslashShape default_shape(const hisq_gauge_s *g, int fl, int fi, int nrhs) {
     DslashShape s;
     const int tiles = (g->geom.vh + 63) / 64;
     const int64_t waves1 = (int64_t)tiles * nrhs;  // with one right-hand side per wavefront
@@ -101,6 +99,11 @@ DslashShape pick_shape(hisq_gauge_s *g, int fl, int fi, int fo, int nrhs, bool e
         s.order = shared_order(waves);
     }
     return s;
+}
+
+DslashShape pick_shape(hisq_gauge_s *g, int fl, int fi, int fo, int nrhs, bool epi) {
+    auto it = g->shapes.find(std::make_tuple(fl, fi, fo, nrhs, (int)epi));
+    return it != g->shapes.end() ? it->second : default_shape(g, fl, fi, nrhs);
 }
 
 bool links_cached(const hisq_gauge_s *g, int fl) { return links_fit_caches(g->links[fl][0].bytes); }

@@ -196,6 +196,8 @@ inline int sloppy_vec_fmt(int sloppy) { return sloppy == HISQ_PREC_FP16L ? F32 :
 // target.  The sloppy FP32 / FP16 copies are compressed when possible.
 inline int links_compressed(const hisq_gauge_s *g, int fmt) { return fmt == F64 ? COMP_NONE : g->comp_mode; }
 
+// Launch shape where the autotuner has installed none.
+DslashShape default_shape(const hisq_gauge_s *g, int fl, int fi, int nrhs);
 DslashShape pick_shape(hisq_gauge_s *g, int fl, int fi, int fo, int nrhs, bool epi);
 bool links_cached(const hisq_gauge_s *g, int fl);
 

@@ -2,6 +2,7 @@
 // GPU).  usage: host_runtime_check CASE; prints "ok", or what failed.
 #include "host_runtime.h"
 
+#include <array>
 #include <new>
 #include <string>
 #include <vector>
@@ -221,11 +222,45 @@ static void create_without_host_memory() {
     CHECK(hisq_gauge_destroy(g) == HISQ_OK);
 }
 
+// The autotuner times the default shape of every number of right-hand sides: where
+// no launch is faster than the default's, that is what it installs.
+static dim3 want_grid, want_block;
+static void tuner_times_the_default() {
+    const double *links = (const double *)0x10000;  // read by kernels only
+    fake::launch_ms = [](dim3 g, dim3 b) {
+        return g.x == want_grid.x && g.y == want_grid.y && b.x == want_block.x ? 0.5f : 1.f;
+    };
+    for (auto &dims : {std::array<int, 4>{8, 8, 8, 8}, {24, 24, 24, 8}, {32, 32, 32, 8}, {48, 48, 48, 12}, {28, 22, 18, 10}}) {
+        hisq_gauge_t g = nullptr;
+        CHECK(hisq_gauge_create(&g, dims.data(), links, links, HISQ_PREC_MASK_ALL, nullptr) == HISQ_OK);
+        for (int prec : {HISQ_PREC_FP64, HISQ_PREC_FP32, HISQ_PREC_FP16S})
+            for (int n = 1; n <= 17; ++n) {
+                void *in = (void *)((uintptr_t)1 << 40), *out = (void *)((uintptr_t)1 << 41);
+                int first[3], now[3];
+                CHECK(hisq_dslash_shape(g, prec, n, 0, first) == HISQ_OK);
+                CHECK(hisq_dslash_multi_rhs(g, 0, prec, n, in, out, nullptr, nullptr, nullptr) == HISQ_OK);
+                want_grid = fake::last_grid;
+                want_block = fake::last_block;
+                CHECK(hisq_autotune(g, prec, n, nullptr, nullptr) == HISQ_OK);
+                CHECK(hisq_dslash_shape(g, prec, n, 0, now) == HISQ_OK);
+                CHECK(hisq_dslash_multi_rhs(g, 0, prec, n, in, out, nullptr, nullptr, nullptr) == HISQ_OK);
+                if (fake::last_grid.x != want_grid.x || fake::last_grid.y != want_grid.y ||
+                    fake::last_block.x != want_block.x) {
+                    std::printf("FAILED %dx%dx%dx%d prec %d n %d: default (%d, %d, %#x), tuned (%d, %d, %#x)\n", dims[0],
+                                dims[1], dims[2], dims[3], prec, n, first[0], first[1], first[2], now[0], now[1], now[2]);
+                    std::exit(1);
+                }
+            }
+        CHECK(hisq_gauge_destroy(g) == HISQ_OK && hisq_release_memory(nullptr) == HISQ_OK);
+    }
+}
+
 int main(int argc, char **argv) {
     const std::string c = argc > 1 ? argv[1] : "";
     if (c == "destroy_other_device") destroy_other_device();
     else if (c == "training_without_memory") training_without_memory();
     else if (c == "create_without_host_memory") create_without_host_memory();
+    else if (c == "tuner_times_the_default") tuner_times_the_default();
     else if (c == "kept_blocks") kept_blocks();
     else if (c == "failed_allocation") failed_allocation();
     else CHECK(!"a known case");
