@@ -55,15 +55,30 @@ size_t dslash_algorithmic_bytes(int fl, int fi, int fo, int64_t vh, int nrhs, bo
 //    4.7, 16^3 x 8 with 2 RHS 7.4 / 6.6, 16^4 8.4 / 8.4, with whole links 11.4 /
 //    9.1, but 24^3 x 8 11.3 / 12.0; FP16S 8^4 5.7 / 4.6, 16^4 7.2 / 6.0, but
 //    24^3 x 8 8.4 / 9.2.
-//  * FP64 from 2, FP32 from 3 and FP16S from 5 right-hand sides: links shared
-//    through LDS, R = ceil(n / 4) per wavefront, at most 16 per workgroup.
-//    48^3 x 12 against the best other shape: FP64 n = 4 355 / 492, n = 16
-//    796 / 1778; FP32 n = 3 147 / 169, n = 8 208 / 278, n = 16 338 / 492;
-//    FP16S n = 5 149 / 178, n = 8 178 / 190, n = 16 320 / 360.
-//  * Fewer: an RHS tile per thread.  FP16S has to convert a link once per
-//    wavefront, which more RHS per thread spread: 48^3 x 12, n = 4 110 (tile 4)
-//    against 127; FP32 n = 2 132 (tile 2) against 138, while a small lattice
-//    gains from twice the wavefronts (24^3 x 8: 12.2 shared, 13.1 tile 2).
+//  * FP64 and FP16 links with FP32 vectors from 2, FP32 and FP16S from 3
+//    right-hand sides: links shared through LDS, R = ceil(n / 4) per wavefront,
+//    at most 16 per workgroup.  48^3 x 12 against the best other shape: FP64
+//    n = 4 355 / 492, n = 16 796 / 1778; FP32 n = 3 147 / 169, n = 8 208 / 278,
+//    n = 16 338 / 492; FP16S n = 5 149 / 178, n = 8 178 / 190, n = 16 320 / 360;
+//    a CG iteration with FP16S n = 3 346 / 449 (36^3 x 12 169 / 221, 32^3 x 8
+//    92.0 / 89.6), with FP16 links and FP32 vectors n = 2 269 / 284 (tile 2,
+//    block 128), n = 4 440 / 483, n = 8 800 / 931.
+//  * FP16S with 4: a tile of 4, which converts a link once for all of them:
+//    48^3 x 12 110 against 127 (the iteration 436 against 426).
+//  * FP16S and FP32 with 2: a tile of 2, while a small lattice in FP32 gains
+//    from twice the wavefronts (24^3 x 8: 12.2 shared, 13.1 tile 2).  CG
+//    iterations with block 64 / 256: FP32 32^3 x 8 84.5 / 86.1, 28^3 x 16 (2744
+//    tiles) 117.1 / 117.6, 36^3 x 8 (2916) 125.0 / 120.9, 40^3 x 8 161 / 156,
+//    48^3 x 12 366 / 368; FP16S 128 / 256: 24 x 32^2 x 16 94.4 / 87.4, 40^3 x 8
+//    115.7 / 113.9, 48^3 x 12 251 / 251.
+//  * FP64 with 2, links past the caches, planes a multiple of 128 KiB apart, 1280
+//    to 4096 tiles: a tile of 2 (CG iterations, shared / block 64): 32^3 x 8
+//    165 / 152, 32^3 x 12 238 / 219, 32^3 x 16 312 / 300, 64 x 32 x 16 x 8
+//    165 / 157, 16 x 32^2 x 12 134 / 127.  Other planes: 36^2 x 32 x 8 207 / 217,
+//    28^3 x 8 123 / 126, 40^3 x 8 313 / 327; fewer or more tiles: 32^2 x 20 x 8
+//    109.1 / 110.1, 32^2 x 16 x 8 90 / 93, 48^2 x 32 x 12 527 / 543, 64 x 32^2 x 16
+//    607 / 615.  That the planes' gathers meet in the same channels is likely,
+//    not counted.
 DslashShape default_shape(const hisq_gauge_s *g, int fl, int fi, int nrhs) {
     DslashShape s;
     const int tiles = (g->geom.vh + 63) / 64;
@@ -83,10 +98,13 @@ DslashShape default_shape(const hisq_gauge_s *g, int fl, int fi, int nrhs) {
     } else if (few) {
         plain(1, 64);
     } else if (fi == H16 && nrhs == 2) {
-        plain(2, 128);
+        plain(2, 256);
     } else if (fi == H16 && nrhs == 4) {
         plain(4, 64);
-    } else if (fi == F32 && nrhs == 2 && tiles >= 2048) {
+    } else if (fl == F32 && nrhs == 2 && tiles >= 2048) {
+        plain(2, tiles < 2816 ? 64 : 256);
+    } else if (fl == F64 && nrhs == 2 && !links_cached(g, fl) && g->geom.vh % 8192 == 0 && tiles > 1280 &&
+               tiles <= 4096) {
         plain(2, 64);
     } else if (!shared_supported(g->geom)) {
         const int maxt = (fl == F64) ? 4 : 8;

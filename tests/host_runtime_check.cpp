@@ -255,12 +255,42 @@ static void tuner_times_the_default() {
     }
 }
 
+// Default shapes of two right-hand sides on both sides of every limit.
+static void two_rhs_shapes() {
+    const double *links = (const double *)0x10000;  // read by kernels only
+    const int SH = shared_order(2);
+    const struct {
+        std::array<int, 4> dims;
+        int prec, tile, block, order;
+    } want[] = {{{32, 32, 32, 8}, HISQ_PREC_FP64, 2, 64, 0},    {{32, 32, 32, 16}, HISQ_PREC_FP64, 2, 64, 0},
+                {{32, 32, 16, 8}, HISQ_PREC_FP64, 1, 128, SH},  {{32, 32, 32, 24}, HISQ_PREC_FP64, 1, 128, SH},
+                {{28, 28, 28, 8}, HISQ_PREC_FP64, 1, 128, SH},  {{24, 24, 24, 8}, HISQ_PREC_FP32, 1, 128, SH},
+                {{32, 32, 32, 8}, HISQ_PREC_FP32, 2, 64, 0},    {{40, 40, 40, 8}, HISQ_PREC_FP32, 2, 256, 0},
+                {{40, 40, 40, 8}, HISQ_PREC_FP16S, 2, 256, 0},  {{40, 40, 40, 8}, HISQ_PREC_FP16L, 1, 128, SH},
+                {{48, 48, 48, 12}, HISQ_PREC_FP16L, 1, 128, SH}};
+    for (auto &w : want) {
+        hisq_gauge_t g = nullptr;
+        CHECK(hisq_gauge_create(&g, w.dims.data(), links, links, HISQ_PREC_MASK_ALL, nullptr) == HISQ_OK);
+        int s[3];
+        for (int epi = 0; epi < 2; ++epi) {
+            CHECK(hisq_dslash_shape(g, w.prec, 2, epi, s) == HISQ_OK);
+            if (s[0] != w.tile || s[1] != w.block || s[2] != w.order) {
+                std::printf("FAILED %dx%dx%dx%d prec %d: (%d, %d, %#x)\n", w.dims[0], w.dims[1], w.dims[2], w.dims[3],
+                            w.prec, s[0], s[1], s[2]);
+                std::exit(1);
+            }
+        }
+        CHECK(hisq_gauge_destroy(g) == HISQ_OK && hisq_release_memory(nullptr) == HISQ_OK);
+    }
+}
+
 int main(int argc, char **argv) {
     const std::string c = argc > 1 ? argv[1] : "";
     if (c == "destroy_other_device") destroy_other_device();
     else if (c == "training_without_memory") training_without_memory();
     else if (c == "create_without_host_memory") create_without_host_memory();
     else if (c == "tuner_times_the_default") tuner_times_the_default();
+    else if (c == "two_rhs_shapes") two_rhs_shapes();
     else if (c == "kept_blocks") kept_blocks();
     else if (c == "failed_allocation") failed_allocation();
     else CHECK(!"a known case");
