@@ -71,14 +71,15 @@ size_t dslash_algorithmic_bytes(int fl, int fi, int fo, int64_t vh, int nrhs, bo
 //    tiles) 117.1 / 117.6, 36^3 x 8 (2916) 125.0 / 120.9, 40^3 x 8 161 / 156,
 //    48^3 x 12 366 / 368; FP16S 128 / 256: 24 x 32^2 x 16 94.4 / 87.4, 40^3 x 8
 //    115.7 / 113.9, 48^3 x 12 251 / 251.
-//  * FP64 with 2, links past the caches, planes a multiple of 128 KiB apart, 1280
-//    to 4096 tiles: a tile of 2 (CG iterations, shared / block 64): 32^3 x 8
-//    165 / 152, 32^3 x 12 238 / 219, 32^3 x 16 312 / 300, 64 x 32 x 16 x 8
-//    165 / 157, 16 x 32^2 x 12 134 / 127.  Other planes: 36^2 x 32 x 8 207 / 217,
-//    28^3 x 8 123 / 126, 40^3 x 8 313 / 327; fewer or more tiles: 32^2 x 20 x 8
-//    109.1 / 110.1, 32^2 x 16 x 8 90 / 93, 48^2 x 32 x 12 527 / 543, 64 x 32^2 x 16
-//    607 / 615.  That the planes' gathers meet in the same channels is likely,
-//    not counted.
+//  * FP64 with 2, links past the caches, over 1280 tiles, planes a multiple of 1
+//    MiB apart, or of 128 KiB with up to 4096 tiles: a tile of 2 (CG iterations,
+//    shared / block 64 / block 256).  1 MiB: 32^3 x 8 165 / 152 / 156, 16^2 x 32^2
+//    163 / 160 / 156, 32^3 x 12 238 / 219 / 228, 24 x 16 x 32^2 236 / 242 / 232,
+//    64 x 32^2 x 16 607 / 615 / 599.  128 KiB: 16 x 32^2 x 12 134 / 127 / 133,
+//    32^2 x 28 x 8 149 / 138 / 145, 48 x 32 x 24 x 8 182 / 177 / 200.  Others share:
+//    36^2 x 32 x 8 207 / 217 / 215, 28^3 x 8 123 / 126, 40^3 x 8 313 / 327 / 326,
+//    32^2 x 16 x 8 (1024 tiles) 90 / 93, 48^2 x 32 x 12 (6912) 527 / 543 / 530.
+//    That the planes' gathers meet in the same channels is likely, not counted.
 DslashShape default_shape(const hisq_gauge_s *g, int fl, int fi, int nrhs) {
     DslashShape s;
     const int tiles = (g->geom.vh + 63) / 64;
@@ -103,9 +104,9 @@ DslashShape default_shape(const hisq_gauge_s *g, int fl, int fi, int nrhs) {
         plain(4, 64);
     } else if (fl == F32 && nrhs == 2 && tiles >= 2048) {
         plain(2, tiles < 2816 ? 64 : 256);
-    } else if (fl == F64 && nrhs == 2 && !links_cached(g, fl) && g->geom.vh % 8192 == 0 && tiles > 1280 &&
-               tiles <= 4096) {
-        plain(2, 64);
+    } else if (fl == F64 && nrhs == 2 && !links_cached(g, fl) && tiles > 1280 &&
+               (g->geom.vh % 65536 == 0 || (g->geom.vh % 8192 == 0 && tiles <= 4096))) {
+        plain(2, g->geom.vh % 65536 == 0 ? 256 : 64);
     } else if (!shared_supported(g->geom)) {
         const int maxt = (fl == F64) ? 4 : 8;
         while (s.tile * 2 <= std::min(nrhs, maxt)) s.tile *= 2;

@@ -262,8 +262,8 @@ static void two_rhs_shapes() {
     const struct {
         std::array<int, 4> dims;
         int prec, tile, block, order;
-    } want[] = {{{32, 32, 32, 8}, HISQ_PREC_FP64, 2, 64, 0},    {{32, 32, 32, 16}, HISQ_PREC_FP64, 2, 64, 0},
-                {{32, 32, 16, 8}, HISQ_PREC_FP64, 1, 128, SH},  {{32, 32, 32, 24}, HISQ_PREC_FP64, 1, 128, SH},
+    } want[] = {{{32, 32, 32, 8}, HISQ_PREC_FP64, 2, 256, 0},   {{48, 32, 24, 8}, HISQ_PREC_FP64, 2, 64, 0},
+                {{32, 32, 16, 8}, HISQ_PREC_FP64, 1, 128, SH},  {{48, 48, 32, 12}, HISQ_PREC_FP64, 1, 128, SH},
                 {{28, 28, 28, 8}, HISQ_PREC_FP64, 1, 128, SH},  {{24, 24, 24, 8}, HISQ_PREC_FP32, 1, 128, SH},
                 {{32, 32, 32, 8}, HISQ_PREC_FP32, 2, 64, 0},    {{40, 40, 40, 8}, HISQ_PREC_FP32, 2, 256, 0},
                 {{40, 40, 40, 8}, HISQ_PREC_FP16S, 2, 256, 0},  {{40, 40, 40, 8}, HISQ_PREC_FP16L, 1, 128, SH},
