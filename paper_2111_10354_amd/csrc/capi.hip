@@ -240,12 +240,9 @@ int hisq_gauge_destroy(hisq_gauge_t g) {
     if (!g) return HISQ_OK;
     // the handle's device, which need not be the current one, has to be idle
     // before its blocks may go to the next allocation there
-    const int device = g->device;
-    int current = device;
-    const bool there = hipGetDevice(&current) == hipSuccess && (current == device || hipSetDevice(device) == hipSuccess);
-    if (there && hipDeviceSynchronize() == hipSuccess) g->recycle();
+    const OnDevice on(g->device);
+    if (on.idle()) g->recycle();
     delete g;
-    if (current != device) (void)hipSetDevice(current);
     return HISQ_OK;
 }
 

@@ -251,7 +251,8 @@ int hisq_nn_create(hisq_nn_t *out, hisq_gauge_t g, int nlayers, const int *chann
 
 int hisq_nn_destroy(hisq_nn_t net) {
     if (!net) return HISQ_OK;
-    (void)hipDeviceSynchronize();
+    const OnDevice on(net->w.device);
+    if (on.idle()) net->recycle();
     delete net;
     return HISQ_OK;
 }

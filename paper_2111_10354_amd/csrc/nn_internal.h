@@ -65,4 +65,5 @@ struct hisq_nn_s {
     int step = 0;
     bool amat_valid = false;
     unsigned long long id = 0;        // unique per network created in this process
+    void recycle() { hisq::recycle_all(w, m, v, g, amat, amat_t, act, scal, train.mem); }  // the device is idle
 };

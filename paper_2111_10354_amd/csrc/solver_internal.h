@@ -102,6 +102,20 @@ struct DevBuf {
 // Frees every kept block (hisq_release_memory).
 int release_kept(size_t *bytes);
 
+// Makes `device` current for a scope.
+struct OnDevice {
+    int device, before;
+    bool ok;
+    explicit OnDevice(int d) : device(d), before(d) {
+        ok = hipGetDevice(&before) == hipSuccess && (before == d || hipSetDevice(d) == hipSuccess);
+    }
+    ~OnDevice() {
+        if (before != device) (void)hipSetDevice(before);
+    }
+    // waits for all work on the device
+    bool idle() const { return ok && hipDeviceSynchronize() == hipSuccess; }
+};
+
 // Recycles buffers of a call that has waited for its stream.
 template <class... B>
 inline void recycle_all(B &...b) {

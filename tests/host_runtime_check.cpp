@@ -70,7 +70,7 @@ static void training_without_memory() {
     const long refused = fake::refused;
     CHECK(hisq_nn_loss_grad(net, 8, v.data(), v.data(), &loss, nullptr, nullptr) == HISQ_OK);
     CHECK(fake::refused == refused);
-    fake::max_block = 3 * have;  // a smaller batch may ask again
+    fake::max_block = 6 * have;  // a smaller batch may ask again
     CHECK(hisq_nn_loss_grad(net, 3, v.data(), v.data(), &loss, nullptr, nullptr) == HISQ_OK);
     CHECK(net->train.cap >= 2);
     const size_t grown = net->train.mem.bytes;
@@ -79,6 +79,30 @@ static void training_without_memory() {
     CHECK(net->train.mem.bytes == grown);
     fake::max_block = ~(size_t)0;
     CHECK(hisq_nn_destroy(net) == HISQ_OK && hisq_gauge_destroy(g) == HISQ_OK);
+}
+
+// A network's blocks go to the next one, once its device is idle.
+static void network_blocks() {
+    const int dims[4] = {8, 8, 8, 8}, ch[4] = {1, 8, 8, 1};
+    hipSetDevice(1);
+    hisq_gauge_t g = make_gauge(dims, HISQ_PREC_MASK(HISQ_PREC_FP32));
+    std::vector<double> thin(4096 * 72, 0.0);
+    CHECK(hisq_gauge_set_thin(g, thin.data(), nullptr) == HISQ_OK);
+    void *in = (void *)((uintptr_t)1 << 40), *out = (void *)((uintptr_t)1 << 41);
+    long mallocs = 0;
+    for (int k = 0; k < 3; ++k) {
+        hisq_nn_t net = nullptr;
+        hipSetDevice(1);
+        if (k == 1) mallocs = fake::mallocs;
+        CHECK(hisq_nn_create(&net, g, 3, ch, nullptr, nullptr) == HISQ_OK);
+        CHECK(hisq_precond_apply(g, net, in, out, nullptr) == HISQ_OK && fake::pending[1] > 0);
+        hipSetDevice(0);
+        CHECK(hisq_nn_destroy(net) == HISQ_OK);
+        int dev = -1;
+        CHECK(hipGetDevice(&dev) == hipSuccess && dev == 0 && fake::pending[1] == 0);
+    }
+    CHECK(fake::mallocs == mallocs);
+    CHECK(hisq_gauge_destroy(g) == HISQ_OK);
 }
 
 // An allocation that fails, with or without kept blocks to give up, leaves no
@@ -291,6 +315,7 @@ int main(int argc, char **argv) {
     else if (c == "create_without_host_memory") create_without_host_memory();
     else if (c == "tuner_times_the_default") tuner_times_the_default();
     else if (c == "two_rhs_shapes") two_rhs_shapes();
+    else if (c == "network_blocks") network_blocks();
     else if (c == "kept_blocks") kept_blocks();
     else if (c == "failed_allocation") failed_allocation();
     else CHECK(!"a known case");
