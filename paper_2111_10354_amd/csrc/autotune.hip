@@ -131,9 +131,6 @@ static std::vector<int> brick_orders(const Geom &G, int fi, int tile) {
     return o;
 }
 
-// RHS split of a shape (bits 24-25 of its order: waves sharing a site's links)
-static int shape_rsplit(const DslashShape &s) { return 1 << ((s.order >> 24) & 3); }
-
 static bool valid_shape(const Geom &geom, int fl, int nrhs, const DslashShape &s) {
     if (const int w = shared_waves(s.order))  // a wave without a right-hand side only repeats another's work
         return shared_built(s.tile, w) && s.tile * (w - 1) < nrhs && order_supported(geom, s.order, s.block);
@@ -149,7 +146,7 @@ static bool valid_shape(const Geom &geom, int fl, int nrhs, const DslashShape &s
     // a split wider than the RHS count only adds idle waves
     int p2 = 1;
     while (p2 < nrhs) p2 <<= 1;
-    if (s.tile * shape_rsplit(s) > p2) return false;
+    if (s.tile * order_rsplit(s.order) > p2) return false;
     return order_supported(geom, s.order, s.block);
 }
 

@@ -17,14 +17,6 @@ Geom make_geom(const int dims[4]) {
     return g;
 }
 
-// Bits 24-25 of a launch's `order`: log2 of the number of waves a site's RHS
-// tiles are split over (RS = 1, 2, 4).  A workgroup of `block` threads then
-// covers block / RS sites, and its RS waves of the same sites apply one RHS
-// tile each: they read the same link units (the later ones from the caches),
-// so each thread holds the accumulators and gathers of one tile only.
-static inline int order_rsplit(int order) { return 1 << ((order >> 24) & 3); }
-static inline int order_tiles(int order) { return order & 0xffffff; }
-
 int dslash_grid_blocks(const Geom &g, int block, int order) {
     if (shared_waves(order) || order == SPLIT_ORDER) return (g.vh + 63) / 64;
     const int sb = block / order_rsplit(order);

@@ -25,14 +25,6 @@
 
 namespace hisq {
 
-// Bits 24-25 of a launch's `order`: log2 of the number of waves a site's RHS
-// tiles are split over (RS = 1, 2, 4).  A workgroup of `block` threads then
-// covers block / RS sites, and its RS waves of the same sites apply one RHS
-// tile each: they read the same link units (the later ones from the caches),
-// so each thread holds the accumulators and gathers of one tile only.
-inline int order_rsplit(int order) { return 1 << ((order >> 24) & 3); }
-inline int order_tiles(int order) { return order & 0xffffff; }
-
 template <class T>
 __device__ __forceinline__ T wave_sum(T v) {
 #pragma unroll

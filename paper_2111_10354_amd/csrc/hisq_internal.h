@@ -146,6 +146,14 @@ __host__ __device__ __forceinline__ int tmarch_first_site(const Geom &g, int i, 
     return (i - q * cols) + q * K * cols;
 }
 
+// Bits 24-25 of a launch's `order`: log2 of the number of waves a site's RHS
+// tiles are split over (RS = 1, 2, 4).  A workgroup of `block` threads then
+// covers block / RS sites, and its RS waves of the same sites apply one RHS
+// tile each: they read the same link units (the later ones from the caches),
+// so each thread holds the accumulators and gathers of one tile only.
+inline int order_rsplit(int order) { return 1 << ((order >> 24) & 3); }
+inline int order_tiles(int order) { return order & 0xffffff; }
+
 // Order in which the workgroups of a shared launch take the 64-site tiles:
 // order[b] = tile of workgroup b.  The tiles are swept in columns of `by`
 // y-rows by `bz` z-planes along t (a tile belongs to the row of its first

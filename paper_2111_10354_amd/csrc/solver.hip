@@ -454,8 +454,9 @@ int cg_solve(hisq_gauge_s *g, double mass, int n, const double *b, double *x, co
             continue;  // re-read the flags
         }
         if (!running) break;
-        // compact once the running RHS fit the next power of two below the
-        // batch (RHS tiles are powers of two)
+        // compact once the running RHS fit the largest power of two below the
+        // batch, so that a batch is copied a few times only; until then a launch
+        // computes the finished RHS of every workgroup that has a running one
         int pow2 = 1;
         while (2 * pow2 < m) pow2 *= 2;
         if (running <= pow2 && running < m && (rc = cg_compact(g, w, slot_of, hs, fin, diag, x, s))) return rc;
