@@ -38,13 +38,14 @@
  * HIP device unless stated otherwise.  The caller owns its buffers; the library
  * never frees them and keeps no reference after a call returns.  A gauge handle
  * owns the library's own packed link copies and solver workspaces.  Memory of
- * destroyed handles and finished calls is kept for the library's next
- * allocations: at most 16 GiB, freed when an allocation of the library fails,
- * if nobody wanted it for five seconds by the next call that allocates, and by
- * hisq_release_memory, which a program calls before it needs nearly all of the
- * device for itself.  `stream` is a hipStream_t (NULL = the default stream).
- * Dslash calls are asynchronous on that stream; solvers order themselves after
- * prior work on it and return when x is written (synchronous).
+ * destroyed handles and networks and of finished calls is kept for the
+ * library's next allocations: at most 16 GiB, freed when an allocation of the
+ * library fails, if nobody wanted it for five seconds by the next call that
+ * allocates, and by hisq_release_memory, which a program calls before it needs
+ * nearly all of the device for itself, and before it resets the device.
+ * `stream` is a hipStream_t (NULL = the default stream).  Dslash calls are
+ * asynchronous on that stream; solvers order themselves after prior work on it
+ * and return when x is written (synchronous).
  *
  * Errors: 0 = OK.  Negative = hard error (nothing usable was written):
  *   -1 invalid argument, -2 HIP runtime error, -3 out of device memory,
@@ -168,8 +169,8 @@ int hisq_gauge_links_compressed(hisq_gauge_t g);
 /* Release the handle and everything it owns (NULL is accepted). */
 int hisq_gauge_destroy(hisq_gauge_t g);
 
-/* Give the memory that the library keeps of destroyed handles and finished
- * calls back to the device; *bytes (may be NULL) is how much it was.  Memory
+/* Give the memory that the library keeps of destroyed handles and networks and
+ * of finished calls back to the device; *bytes (may be NULL) is how much it was.  Memory
  * of live handles and networks stays.  -2: the runtime refused some of it (as
  * while a thread captures a graph), which stays kept. */
 int hisq_release_memory(size_t *bytes);

@@ -31,16 +31,16 @@
 //     load of a wavefront is 1 KiB in one piece, where the caller's layout
 //     (576 bytes from site to site) touches 64 cache lines per load;
 //   * sites are swept in columns along t, an eighth of the sweep per XCD
-//     (Sweep): 48^3 x 12 in 13.2 ms against 14.7 ms with whole (z, t) planes;
+//     (Sweep): 48^3 x 12 in 13.2 ms against 14.7 ms with whole (z, t) planes (in
+//     the same run);
 //   * a staple issues the loads of five matrices before its first product and
 //     the kernels take the registers for that (one or two wavefronts per
 //     SIMD).  Scheduled by the compiler at three or four wavefronts it was
 //     15.4 ms: each of ~20 waits was a round trip, and the sites in flight
 //     did not fit the L2 (T pass: 2.85 GB from beyond the L2, now 1.2 GB).
-// 48^3 x 12: 51 ms in 150 canonical-layout launches before, 13.2 ms now
-// (T 0.33, B 0.67, V 0.39 and 0.68 with Lepage, each 4 times per level; 12.7 in
-// a later run);
-// 96^3 x 24: 840 ms before, 203 ms now.
+// 48^3 x 12: 51 ms in 150 canonical-layout launches before, 12.7 ms now
+// (T 0.33, B 0.67, V 0.39 and 0.68 with Lepage, each 4 times per level);
+// 96^3 x 24: 840 ms before, 204 ms now.
 //
 // Scratch: the two outputs hold intermediate fields until their own pass
 // writes them, and one workspace of six one-direction fields comes on top:
