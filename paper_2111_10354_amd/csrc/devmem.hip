@@ -148,7 +148,7 @@ int DevBuf::alloc(size_t n) {
 }
 
 void DevBuf::release() {
-    if (p) (void)hipFree(p);
+    if (p && hipFree(p) != hipSuccess) (void)hipGetLastError();
     p = nullptr;
     bytes = held = 0;
 }

@@ -112,8 +112,13 @@ struct OnDevice {
     ~OnDevice() {
         if (before != device) (void)hipSetDevice(before);
     }
-    // waits for all work on the device
-    bool idle() const { return ok && hipDeviceSynchronize() == hipSuccess; }
+    // Waits for all work on the device; false, and no error left behind, where
+    // that is refused (while a thread captures a graph).
+    bool idle() const {
+        if (ok && hipDeviceSynchronize() == hipSuccess) return true;
+        (void)hipGetLastError();
+        return false;
+    }
 };
 
 // Recycles buffers of a call that has waited for its stream.

@@ -29,7 +29,7 @@ struct Block {
 inline std::map<void *, Block> blocks;
 inline long mallocs = 0, frees = 0, refused = 0, serial = 0;
 inline size_t total = 0, max_block = ~(size_t)0, budget = ~(size_t)0;
-inline bool free_fails = false;
+inline bool free_fails = false, sync_fails = false;
 inline long pending[2] = {0, 0};  // launches that nothing has waited for, per device
 inline double clock_shift = 0.0;  // seconds added to the monotonic clock
 inline dim3 last_grid, last_block;
@@ -90,7 +90,10 @@ hipError_t hipFree(void *p) {
 
 hipError_t hipGetDevice(int *d) { return *d = fake::device, hipSuccess; }
 hipError_t hipSetDevice(int d) { return fake::device = d, hipSuccess; }
-hipError_t hipDeviceSynchronize() { return fake::pending[fake::device] = 0, hipSuccess; }
+hipError_t hipDeviceSynchronize() {
+    if (fake::sync_fails) return fake::fail(hipErrorStreamCaptureUnsupported);
+    return fake::pending[fake::device] = 0, hipSuccess;
+}
 hipError_t hipGetLastError() {
     const hipError_t e = fake::last;
     fake::last = hipSuccess;

@@ -81,6 +81,21 @@ static void training_without_memory() {
     CHECK(hisq_nn_destroy(net) == HISQ_OK && hisq_gauge_destroy(g) == HISQ_OK);
 }
 
+// Destroying while the runtime refuses to wait or to free (a thread captures a
+// graph) leaves no error for the next launch check.
+static void destroy_while_refused() {
+    const int dims[4] = {8, 8, 8, 8}, ch[3] = {1, 8, 1};
+    hisq_gauge_t g = make_gauge(dims, HISQ_PREC_MASK(HISQ_PREC_FP32));
+    hisq_nn_t net = nullptr;
+    CHECK(hisq_nn_create(&net, g, 2, ch, nullptr, nullptr) == HISQ_OK);
+    fake::sync_fails = fake::free_fails = true;
+    CHECK(hisq_nn_destroy(net) == HISQ_OK && hipGetLastError() == hipSuccess);
+    CHECK(hisq_gauge_destroy(g) == HISQ_OK && hipGetLastError() == hipSuccess);
+    fake::sync_fails = fake::free_fails = false;
+    size_t freed = 1;
+    CHECK(hisq_release_memory(&freed) == HISQ_OK && freed <= 8);  // nothing was kept of either
+}
+
 // A network's blocks go to the next one, once its device is idle.
 static void network_blocks() {
     const int dims[4] = {8, 8, 8, 8}, ch[4] = {1, 8, 8, 1};
@@ -316,6 +331,7 @@ int main(int argc, char **argv) {
     else if (c == "tuner_times_the_default") tuner_times_the_default();
     else if (c == "two_rhs_shapes") two_rhs_shapes();
     else if (c == "network_blocks") network_blocks();
+    else if (c == "destroy_while_refused") destroy_while_refused();
     else if (c == "kept_blocks") kept_blocks();
     else if (c == "failed_allocation") failed_allocation();
     else CHECK(!"a known case");

@@ -29,7 +29,7 @@ def program(tmp_path_factory):
 
 @pytest.mark.parametrize("case", ["destroy_other_device", "failed_allocation", "training_without_memory",
                                   "kept_blocks", "create_without_host_memory", "tuner_times_the_default",
-                                  "two_rhs_shapes", "network_blocks"])
+                                  "two_rhs_shapes", "network_blocks", "destroy_while_refused"])
 def test_host_code(program, case):
     r = subprocess.run([str(program), case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout == "ok\n", r.stdout + r.stderr
